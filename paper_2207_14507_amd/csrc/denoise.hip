@@ -8,17 +8,16 @@
 //               detail subbands to their quadrants of the coefficient plane.  Level 1
 //               reads the caller's image and extends it by mirroring past its last row
 //               and column (to a multiple of 16 on each side).
-//   k_wiener    per detail subband: the windowed means of c^2 over 3x3, 5x5, 7x7 and
-//               9x9 (zero outside the subband, separable sums in LDS), the smallest
-//               minus s0^2 clipped at zero as the signal variance v, and the part the
-//               Wiener estimate removes, c s0^2 / (v + s0^2).
-//   k_dwt_inv   one level of the inverse transform (the adjoint, periodic) from the
-//               approximation (zero at the coarsest level: the residual keeps none of
-//               it) and the Wiener-removed detail parts; level 1 writes the cropped
-//               residual.
+//   k_dwt_inv   one level of the Wiener step and the inverse transform.  Per detail
+//               subband: the windowed means of c^2 over 3x3, 5x5, 7x7 and 9x9 (zero
+//               outside the subband), the smallest minus s0^2 clipped at zero as the
+//               signal variance v, and the part the Wiener estimate removes,
+//               c s0^2 / (v + s0^2).  From those and the approximation (zero at the
+//               coarsest level: the residual keeps none of it) the adjoint transform
+//               (periodic); level 1 writes the cropped residual.
 //
 // All arithmetic is fp32.  Every kernel is a streaming pass: its input tile and halo
-// are read once into LDS, its outputs written once.
+// are read once, its outputs written once.
 #include "kernels.hpp"
 
 namespace prnu {
@@ -122,137 +121,188 @@ __global__ __launch_bounds__(FT) void k_dwt_fwd(const float* __restrict__ in, in
 }
 
 // ---------------------------------------------------------------------------
-// Wiener step on the detail subbands of one level.  Output tile WY rows x WX columns,
-// halo 4 (the 9x9 window's reach).  A thread owns one column and WR consecutive rows:
-// it forms the horizontal sums of c^2 of the WR + 8 rows it needs in registers (each
-// coefficient read from LDS once per window offset) and slides the vertical sums
-// down its rows, so a coefficient costs about 20 LDS reads instead of the 40 of a
-// separate horizontal pass through LDS.
+// Wiener step and inverse level.  Output tile IY x IX of the level's rows x cols plane:
+// it takes CY x CX coefficients of each subband (the filter's reach is 3 back).  A wave
+// takes one subband and a run of coefficient rows, a raw coefficient column per lane: the
+// rows come straight from memory into registers, the windows' horizontal sums from the
+// neighbouring lanes, the vertical ones from the last nine rows; only the results go to
+// LDS.
+//
+// Level 1 of 16 1080p images (coefficients 176 MB in, residuals 133 MB out): 106 us, bound
+// by its vector instructions (issue slots 76% busy: 18 per raw coefficient, 38 per
+// result), where the variances as a pass of their own took 88 us and wrote and read
+// 200 MB more, and the inverse after it 88 us.  64 x 96: a raw column per lane with both
+// halos (59 of 64 lanes, 51 of them results); 32 rows cost 6% more at 1080p (more halo)
+// for 4% less at 333 x 501.  With the raw tile in LDS and nine reads per coefficient and
+// row the kernel took 115 us, two columns per thread 140 us (106 VGPRs, two workgroups
+// per CU instead of three).
+constexpr int IY = 64, IX = 96;
+constexpr int CY = IY / 2 + 3, CX = IX / 2 + 3;
+constexpr int WH = 4;            // the 9 x 9 window's reach
+constexpr int WN = IY / 16;      // runs of rows per subband
+constexpr int WR = (CY + WN - 1) / WN;           // rows of a run
+constexpr int WRE = (IY / 2 + WN - 2) / (WN - 1);  // rows of a run in a tile of the first rows
+constexpr int IT = 3 * WN * 64;
+static_assert(CX + 2 * WH <= 64 && 7 + WH + IX / 2 + WH <= 64, "a raw column per lane, wrapped ones too");
+constexpr int VS = CX | 1;  // LDS row stride of the vertical synthesis (read at every second column)
 
-constexpr int WX = 64, WY = 32, WH = 4, WT = 256, WR = WY / (WT / WX);
-constexpr int WEX = WX + 2 * WH, WEY = WY + 2 * WH;
+// v of the previous (next) lane, zero into the first (last).
+__device__ __forceinline__ float lane_prev(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+__device__ __forceinline__ float lane_next(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));  // wave_shl:1
+}
 
-// coef / out: coefficient planes (stride rs, image stride is); the level's subbands
-// are sr x sc at (0, sc), (sr, 0), (sr, sc).
-__global__ __launch_bounds__(WT) void k_wiener(const float* __restrict__ coef, float* __restrict__ out, int64_t is,
-                                               int64_t rs, int sr, int sc, float s2) {
-  __shared__ float cs[WEY][WEX + 1];  // coefficients of the tile and halo, zero outside the subband
-  const int img = blockIdx.z / 3, band = blockIdx.z % 3;
-  const int oy = band == 0 ? 0 : sr, ox = band == 1 ? 0 : sc;
-  const int y0 = blockIdx.y * WY, x0 = blockIdx.x * WX;
-  const float* cb = coef + (int64_t)img * is + (int64_t)oy * rs + ox;
-  float* ob = out + (int64_t)img * is + (int64_t)oy * rs + ox;
-  {
-    constexpr int NL = (WEY * WEX + WT - 1) / WT;
-    float v[NL];
+// The removed part of a coefficient c whose windows' sums of c^2 are t3, t5, t7, t9.
+__device__ __forceinline__ float removed(float c, float t3, float t5, float t7, float t9, float s2) {
+  const float m = fminf(fminf(t3 * (1.f / 9.f), t5 * (1.f / 25.f)), fminf(t7 * (1.f / 49.f), t9 * (1.f / 81.f)));
+  const float v = fmaxf(0.f, m - s2);
+  return s2 > 0.f ? c * (s2 / (v + s2)) : 0.f;
+}
+
+// The removed parts of R rows of one subband (column x of its first row at src, row
+// stride rs), rows n.. (n < 0: the far end's last rows, n + ro..).  Raw rows outside the
+// subband, and lanes that hold no column of it (xin false), count as zero.  The results
+// of the first `rows` rows go to out (LDS, row stride CX) where put.
+template <int R>
+__device__ __forceinline__ void wiener_rows(const float* src, int64_t rs, unsigned x, bool xin, int n, int ro, int rows,
+                                            float s2, float* out, bool put) {
+  const int first = n < 0 ? -ro : 0;  // the subband's first row in the run's numbering
+  float v[R + 8], h[4][R + 8];
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int i = threadIdx.x + k * WT;
-      const int r = i / WEX, c = i % WEX;
-      const int y = y0 + r - WH, x = x0 + c - WH;
-      v[k] = (i < WEY * WEX && y >= 0 && y < sr && x >= 0 && x < sc) ? cb[(int64_t)y * rs + x] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int i = threadIdx.x + k * WT;
-      if (i < WEY * WEX) cs[i / WEX][i % WEX] = v[k];
-    }
-  }
-  __syncthreads();
-  const int tx = threadIdx.x % WX, r0 = (threadIdx.x / WX) * WR;
-  const int x = x0 + tx;
-  if (x >= sc) return;
-  // horizontal sums of c^2 over 3, 5, 7, 9 columns for tile rows r0 - 4 .. r0 + WR + 3
-  float h3[WR + 8], h5[WR + 8], h7[WR + 8], h9[WR + 8];
-#pragma unroll
-  for (int k = 0; k < WR + 8; ++k) {
-    float q[9];
-#pragma unroll
-    for (int b = 0; b < 9; ++b) {
-      const float v = cs[r0 + k][tx + b];
-      q[b] = v * v;
-    }
-    h3[k] = q[3] + q[4] + q[5];
-    h5[k] = h3[k] + q[2] + q[6];
-    h7[k] = h5[k] + q[1] + q[7];
-    h9[k] = h7[k] + q[0] + q[8];
+  for (int k = 0; k < R + 8; ++k) {
+    const int y = n - WH + k - first;
+    v[k] = src[(int64_t)(y >= 0 && y < ro ? y : 0) * rs + x];
   }
 #pragma unroll
-  for (int j = 0; j < WR; ++j) {
-    const int y = y0 + r0 + j;
-    if (y < sr) {
-      const int k = j + WH;  // this row's index in the h arrays
-      const float t3 = h3[k - 1] + h3[k] + h3[k + 1];
-      const float t5 = h5[k - 2] + h5[k - 1] + h5[k] + h5[k + 1] + h5[k + 2];
-      float t7 = 0.f, t9 = 0.f;
+  for (int k = 0; k < R + 8; ++k) {
+    const int y = n - WH + k - first;
+    v[k] = xin && y >= 0 && y < ro ? v[k] : 0.f;
+    const float q = v[k] * v[k];
+    float l = lane_prev(q), r = lane_next(q);
+    h[0][k] = l + q + r;
 #pragma unroll
-      for (int a = -3; a <= 3; ++a) t7 += h7[k + a];
-#pragma unroll
-      for (int a = -4; a <= 4; ++a) t9 += h9[k + a];
-      const float m = fminf(fminf(t3 * (1.f / 9.f), t5 * (1.f / 25.f)), fminf(t7 * (1.f / 49.f), t9 * (1.f / 81.f)));
-      const float v = fmaxf(0.f, m - s2);
-      const float c = cs[r0 + k][tx + WH];
-      ob[(int64_t)y * rs + x] = s2 > 0.f ? c * (s2 / (v + s2)) : 0.f;
+    for (int w = 1; w < 4; ++w) {
+      l = lane_prev(l);
+      r = lane_next(r);
+      h[w][k] = h[w - 1][k] + l + r;
+    }
+    if (k >= 8) {
+      const int j = k - 8, m = j + WH;
+      // sums of two and four rows, each formed once for the outputs that share it
+      auto two = [&](int w, int i) { return h[w][i] + h[w][i + 1]; };
+      auto four = [&](int w, int i) { return two(w, i) + two(w, i + 2); };
+      const float t3 = two(0, m - 1) + h[0][m + 1];
+      const float t5 = four(1, m - 2) + h[1][m + 2];
+      const float t7 = four(2, m - 3) + (two(2, m + 1) + h[2][m + 3]);
+      const float t9 = (four(3, m - 4) + four(3, m)) + h[3][m + 4];
+      const float g = removed(v[m], t3, t5, t7, t9, s2);
+      if (put && j < rows) out[j * CX] = g;
     }
   }
 }
 
-// ---------------------------------------------------------------------------
-// Inverse level.  Output tile IY x IX of the level's rows x cols plane.
+// The removed part of the coefficient (n, m) of a subband of ro x co, element by element:
+// for subbands shorter than 7, which a tile of the first rows or columns holds several
+// times over.
+__device__ __forceinline__ float wiener_small(const float* src, int64_t rs, int n, int m, int ro, int co, float s2) {
+  float t3 = 0.f, t5 = 0.f, t7 = 0.f, t9 = 0.f;
+#pragma unroll 1
+  for (int a = -WH; a <= WH; ++a) {
+    if (n + a < 0 || n + a >= ro) continue;
+#pragma unroll 1
+    for (int b = -WH; b <= WH; ++b) {
+      if (m + b < 0 || m + b >= co) continue;
+      const float v = src[(int64_t)(n + a) * rs + m + b];
+      const int w = max(abs(a), abs(b));
+      const float q = v * v;
+      t9 += q;
+      t7 += w <= 3 ? q : 0.f;
+      t5 += w <= 2 ? q : 0.f;
+      t3 += w <= 1 ? q : 0.f;
+    }
+  }
+  return removed(src[(int64_t)n * rs + m], t3, t5, t7, t9, s2);
+}
 
-constexpr int IY = 32, IX = 64, IT = 256;
-constexpr int ICY = IY / 2 + 3, ICX = IX / 2 + 3;  // coefficient tile with the filter's reach
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// ll: approximation plane (ro x co, stride ll_rs, image stride ll_is) or null (zero);
-// det: detail parts, quadrants as in k_dwt_fwd.  out: rows x cols plane (stride out_rs,
-// image stride out_is), only its first M rows and N columns written.
-__global__ __launch_bounds__(IT) void k_dwt_inv(const float* __restrict__ ll, int64_t ll_is, int64_t ll_rs,
-                                                const float* __restrict__ det, int64_t det_is, int64_t det_rs,
-                                                int rows, int cols, int M, int N, float* __restrict__ out,
-                                                int64_t out_is, int64_t out_rs) {
-  __shared__ float s[4][ICY][ICX + 1];  // LL, LH, HL, HH
-  __shared__ float vl[IY][ICX + 1], vh[IY][ICX + 1];
-  const int img = blockIdx.z;
+// ll: approximation plane (ro x co, stride ll_rs, image stride ll_is) or null (zero: the
+// residual keeps none of the coarsest); det: coefficient planes, quadrants as in
+// k_dwt_fwd.  out: rows x cols plane (stride out_rs, image stride out_is), only its first
+// M rows and N columns written.
+__global__ __launch_bounds__(IT, 6) void k_dwt_inv(const float* __restrict__ ll, int64_t ll_is, int64_t ll_rs,
+                                                     const float* __restrict__ det, int64_t det_is, int64_t det_rs,
+                                                     int rows, int cols, int M, int N, float s2,
+                                                     float* __restrict__ out, int64_t out_is, int64_t out_rs) {
+  __shared__ float s[3][CY][CX], a[CY][CX];  // removed parts (LH, HL, HH) and LL
+  __shared__ float vl[IY][VS], vh[IY][VS];   // vertical synthesis
+  const int img = blockIdx.z, tid = threadIdx.x;
   const int ro = rows / 2, co = cols / 2;
   const int y0 = blockIdx.y * IY, x0 = blockIdx.x * IX;
   const int n0 = y0 / 2 - 3, m0 = x0 / 2 - 3;
-  const float* d = det + (int64_t)img * det_is;
-  const float* a = ll ? ll + (int64_t)img * ll_is : nullptr;
   {
-    constexpr int NL = (ICY * ICX + IT - 1) / IT;
-    float v[NL][4];
+    // the wave's index, and with it every row's address, in scalar registers
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float* d = det + (int64_t)img * det_is;
+    // LL rows, requested first
+    constexpr int NC = (CY + 3 * WN - 1) / (3 * WN);
+    float va[NC];
+    const unsigned xa = lane < CX ? (unsigned)wrap(m0 + lane, co) : 0u;
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int i = threadIdx.x + k * IT;
-      if (i < ICY * ICX) {
-        const int n = wrap(n0 + i / ICX, ro), m = wrap(m0 + i % ICX, co);
-        v[k][0] = a ? a[(int64_t)n * ll_rs + m] : 0.f;
-        v[k][1] = d[(int64_t)(n + ro) * det_rs + m];
-        v[k][2] = d[(int64_t)n * det_rs + m + co];
-        v[k][3] = d[(int64_t)(n + ro) * det_rs + m + co];
+    for (int k = 0; k < NC; ++k)
+      va[k] = ll ? (ll + (int64_t)img * ll_is + (int64_t)wrap(n0 + w + k * 3 * WN, ro) * ll_rs)[xa] : 0.f;
+    const int band = w / WN, run = w % WN;
+    const float* src = d + (band == 1 ? 0 : (int64_t)ro * det_rs) + (band == 0 ? 0 : co);
+    float* sb = &s[band][0][0];
+    if (min(ro, co) < 3 + WH) {
+      for (int i = run * 64 + lane; i < CY * CX; i += WN * 64)
+        sb[i] = wiener_small(src, det_rs, wrap(n0 + i / CX, ro), wrap(m0 + i % CX, co), ro, co, s2);
+    } else {
+      // The lane's column.  In a tile of the first columns, lanes 0..6 hold the far end's
+      // last seven (the synthesis is periodic, the windows are not), four lanes zeros.
+      int m = m0 - WH + lane;
+      bool in = m < co && lane < CX + 2 * WH, res = lane >= WH && lane < WH + CX;
+      if (m0 < 0) {
+        const bool far = lane < 7;
+        m = far ? lane - 7 : lane - 7 - WH;
+        in = far || (m >= 0 && m < co && m < IX / 2 + WH);
+        res = far ? m >= -3 : m >= 0 && m < IX / 2;
+      }
+      const unsigned x = in ? (unsigned)(m < 0 ? m + co : m) : 0u;
+      float* o = sb + (res ? m - m0 : 0);
+      if (n0 < 0) {
+        // a tile of the first rows: the far end's last three are a run of their own
+        if (run == 0)
+          wiener_rows<3>(src, det_rs, x, in, -3, ro, 3, s2, o, res);
+        else
+          wiener_rows<WRE>(src, det_rs, x, in, (run - 1) * WRE, ro, min(WRE, IY / 2 - (run - 1) * WRE), s2,
+                           o + (3 + (run - 1) * WRE) * CX, res);
+      } else {
+        wiener_rows<WR>(src, det_rs, x, in, n0 + run * WR, ro, min(WR, CY - run * WR), s2, o + run * WR * CX, res);
       }
     }
 #pragma unroll
-    for (int k = 0; k < NL; ++k) {
-      const int i = threadIdx.x + k * IT;
-      if (i < ICY * ICX) {
-#pragma unroll
-        for (int b = 0; b < 4; ++b) s[b][i / ICX][i % ICX] = v[k][b];
-      }
+    for (int k = 0; k < NC; ++k) {
+      const int r = w + k * 3 * WN;
+      if (lane < CX && r < CY) a[r][lane] = va[k];
     }
   }
   __syncthreads();
   // vertical: output row y takes coefficient rows y/2 - j (j = 0..3) with taps y%2 + 2j
   // (y0 is even).  A thread takes one coefficient column and 8 output rows, which
   // need 7 coefficient rows of each subband: read into registers once.
-  static_assert(IY % 8 == 0 && (IY / 8) * ICX <= IT, "one vertical work item per thread");
-  if (threadIdx.x < (IY / 8) * ICX) {
-    const int c = threadIdx.x % ICX, g = threadIdx.x / ICX;
+  static_assert(IY % 8 == 0, "whole vertical work items");
+  for (int i = tid; i < (IY / 8) * CX; i += IT) {
+    const int c = i % CX, g = i / CX;
     float q[4][7];
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int t = 0; t < 7; ++t) q[0][t] = a[4 * g + t][c];
 #pragma unroll
-      for (int t = 0; t < 7; ++t) q[b][t] = s[b][4 * g + t][c];
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int t = 0; t < 7; ++t) q[b + 1][t] = s[b][4 * g + t][c];
 #pragma unroll
     for (int rr = 0; rr < 8; ++rr) {
       const int p = rr & 1, nb = rr / 2 + 3;  // local coefficient row of j = 0, minus 4g
@@ -268,19 +318,31 @@ __global__ __launch_bounds__(IT) void k_dwt_inv(const float* __restrict__ ll, in
     }
   }
   __syncthreads();
+  // horizontal: four outputs of a row per thread, from five columns of each half
   float* o = out + (int64_t)img * out_is;
-  for (int i = threadIdx.x; i < IY * IX; i += IT) {
-    const int r = i / IX, c = i % IX;
+  const int yend = min(rows, M), xend = min(cols, N);
+  for (int i = tid; i < IY * IX / 4; i += IT) {
+    const int r = i / (IX / 4), c = i % (IX / 4) * 4;
     const int y = y0 + r, x = x0 + c;
-    if (y >= rows || x >= cols || y >= M || x >= N) continue;
-    const int p = x & 1, mb = c / 2 + 3;
-    float v = 0.f;
+    if (y >= yend || x >= xend) continue;
+    float l[5], h[5], v[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = p + 2 * j;
-      v = fmaf(kH[k], vl[r][mb - j], fmaf(kG[k], vh[r][mb - j], v));
+    for (int t = 0; t < 5; ++t) l[t] = vl[r][c / 2 + t], h[t] = vh[r][c / 2 + t];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int p = t & 1, mb = t / 2 + 3;
+      v[t] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[t] = fmaf(kH[p + 2 * j], l[mb - j], fmaf(kG[p + 2 * j], h[mb - j], v[t]));
     }
-    o[(int64_t)y * out_rs + x] = v;
+    float* po = o + (int64_t)y * out_rs + x;
+    if (x + 4 <= xend) {
+      *reinterpret_cast<f4u*>(po) = f4u{v[0], v[1], v[2], v[3]};
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (x + t < xend) po[t] = v[t];
+    }
   }
 }
 
@@ -290,7 +352,7 @@ int residual_padded(int n) { return (n + 15) / 16 * 16; }
 
 size_t residual_workspace_floats(int M, int N) {
   const size_t M2 = (size_t)residual_padded(M), N2 = (size_t)residual_padded(N);
-  return 2 * M2 * N2 + (M2 / 2) * (N2 / 2) + (M2 / 4) * (N2 / 4);
+  return M2 * N2 + (M2 / 2) * (N2 / 2) + (M2 / 4) * (N2 / 4);
 }
 
 hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L, int M, int N, float sigma0,
@@ -299,10 +361,9 @@ hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L
   const int M2 = residual_padded(M), N2 = residual_padded(N);
   const int64_t P = (int64_t)M2 * N2;
   const int64_t per = (int64_t)residual_workspace_floats(M, N);
-  // per image: coefficient plane C, Wiener-part plane D, approximation planes T1, T2
+  // per image: coefficient plane C, approximation planes T1, T2
   float* C = ws;
-  float* D = ws + P;
-  float* T1 = ws + 2 * P;
+  float* T1 = ws + P;
   float* T2 = T1 + (int64_t)(M2 / 2) * (N2 / 2);
   constexpr int kLevels = 4;
   // forward: level l reads a rows x cols plane and writes rows/2 x cols/2 subbands
@@ -322,31 +383,21 @@ hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L
     k_dwt_fwd<<<grid, FT, 0, s>>>(src, sis, srs, rows, cols, mm, nn, dst_ll, per, cols / 2, C, per, N2);
   }
   const float s2 = sigma0 * sigma0;
-  for (int l = 1; l <= kLevels; ++l) {
-    const int sr = M2 >> l, sc = N2 >> l;
-    dim3 grid((unsigned)((sc + WX - 1) / WX), (unsigned)((sr + WY - 1) / WY), (unsigned)(3 * L));
-    k_wiener<<<grid, WT, 0, s>>>(C, D, per, N2, sr, sc, s2);
-  }
   // inverse: level l rebuilds the rows x cols plane from its rows/2 x cols/2 subbands.
-  // Approximations: level 4 starts from zero and writes T2, level 3 reads T2 and writes
-  // T1, level 2 reads T1 and writes the (free) top-left quadrant of C, level 1 reads it
-  // and writes the cropped residual.
+  // Approximations: level 4 starts from zero and writes T1, level 3 reads T1 and writes
+  // T2, level 2 reads T2 and writes T1, level 1 reads it and writes the cropped residual.
   for (int l = kLevels; l >= 1; --l) {
     const int rows = M2 >> (l - 1), cols = N2 >> (l - 1);
-    const float* src_ll = nullptr;
-    int64_t src_rs = 0;
-    if (l == 3) src_ll = T2, src_rs = cols / 2;
-    if (l == 2) src_ll = T1, src_rs = cols / 2;
-    if (l == 1) src_ll = C, src_rs = N2;
+    const float* src_ll = l == kLevels ? nullptr : (l % 2 == 1 ? T1 : T2);
     float* dst = out;
     int64_t dis = out_is, drs = out_rs;
     int mm = M, nn = N;
     if (l > 1) {
-      dst = l == 4 ? T2 : (l == 3 ? T1 : C);
-      dis = per, drs = l == 2 ? N2 : cols, mm = rows, nn = cols;
+      dst = l % 2 == 0 ? T1 : T2;
+      dis = per, drs = cols, mm = rows, nn = cols;
     }
     dim3 grid((unsigned)((cols + IX - 1) / IX), (unsigned)((rows + IY - 1) / IY), (unsigned)L);
-    k_dwt_inv<<<grid, IT, 0, s>>>(src_ll, per, src_rs, D, per, N2, rows, cols, mm, nn, dst, dis, drs);
+    k_dwt_inv<<<grid, IT, 0, s>>>(src_ll, per, cols / 2, C, per, N2, rows, cols, mm, nn, s2, dst, dis, drs);
   }
   return hipGetLastError();
 }

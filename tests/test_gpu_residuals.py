@@ -69,6 +69,18 @@ def test_residuals_match_oracle(P, ctx, M, N):
         check(f"{M}x{N} image {l}", W[l], I[l], 3.0)
 
 
+@pytest.mark.parametrize("M,N", [(64, 96), (128, 192), (65, 97), (130, 290), (112, 112), (96, 400), (400, 96),
+                                 (16, 640), (640, 16)])
+def test_residuals_at_the_inverse_tiles_edges(P, ctx, M, N):
+    """The inverse's tiles of 64 x 96: one and several whole tiles, one row and column
+    more; the coarsest subband 7 long (the shortest whose windows stay inside a tile's
+    wrapped reach) and 6 in one direction; one coefficient row or column."""
+    I, _ = images(8, 2, M, N)
+    W = P.prnu_extract_residuals(ctx, I, 3.0)
+    for l in range(2):
+        check(f"{M}x{N} image {l}", W[l], I[l], 3.0)
+
+
 @pytest.mark.parametrize("sigma0", [0.5, 10.0, 1e4])
 def test_other_noise_levels(P, ctx, sigma0):
     I, _ = images(2, 1, 96, 160)
