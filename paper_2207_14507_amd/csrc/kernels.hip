@@ -13,9 +13,11 @@
 //                   product (all-shift energy of Eq. 3), inverse column DFT; only the
 //                   rows |dy| <= R + 5 (peak search + exclusion reach) are stored.
 //   k_band_rowifft  inverse row DFT of pairs of stored rows (Hermitian-extended);
-//                   only the columns |dx| <= R + 5 are stored.
-//   k_pce           signed peak over |dy|,|dx| <= R, FP64 energy of the 11x11
-//                   exclusion block, PCE and NCC at the peak.
+//                   only the columns |dx| <= R + 5 are stored.  Also the rows' largest
+//                   value over |dx| <= R (rows |dy| <= R).
+//   k_pce           signed peak over |dy|,|dx| <= R: the row pair with the largest value,
+//                   then its place in those two rows;
+//                   FP64 energy of the 11x11 exclusion block, PCE and NCC at the peak.
 //
 // Frames smaller than the fingerprint (M - ey rows, N - ex columns) are zero-padded to
 // its size; the stored rows and columns then reach from -R - 5 to ey + R + 5 and
@@ -216,6 +218,7 @@ __device__ __forceinline__ Batch fresh(const Batch& bt) {
   opaque(b.win);
   opaque(b.norm_part);
   opaque(b.energy_part);
+  opaque(b.peak_part);
   opaque(b.rec);
   opaque(b.twM);
   opaque(b.twMi);
@@ -704,6 +707,22 @@ __global__ __launch_bounds__(T, 4) void k_col_dyn(Batch bt) {
 
 // ---------------------------------------------------------------------------
 
+// The largest of the wave's values, in every lane: six DPP steps (shifts within rows of
+// 16 lanes, then the rows' last lanes broadcast onward), no LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max(float v) {
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, ROWS, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = dpp_max<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_max<0x112, 0xf>(v);
+  v = dpp_max<0x114, 0xf>(v);
+  v = dpp_max<0x118, 0xf>(v);
+  v = dpp_max<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_max<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 // One tile (candidate, pair of band rows) w of nc candidates.
 template <int N, int T>
 __device__ __forceinline__ void band_rowifft_tile(const Batch& bt, const int nc, const int tile, const int tid) {
@@ -808,6 +827,12 @@ __device__ __forceinline__ void band_rowifft_tile(const Batch& bt, const int nc,
   // window narrower than 2 Ns on either side can only hold q in {0, 1, R-2, R-1}.
   static_assert(PL::NB == PL::NS, "last pass: butterfly j writes columns j + q Ns");
   const bool narrow = PL::R >= 4 && RGT < 2 * PL::NS;
+  // The largest value of the two rows in the peak's range (the window without its 5
+  // outermost rows and columns), per wave: the PCE kernel then reads those and two rows
+  // instead of the window (129 x 129 values at R = 64, 489 x 769 for 720p frames in a
+  // 1080p fingerprint).  NaN is passed over.
+  const bool pa = ra >= 5 && ra < BR - 5, pb = rb >= 5 && rb < BR - 5;
+  float best = -INFINITY;
 #pragma unroll
   for (int r = 0; r < PL::ROUNDS; ++r) {
     const int j = tid + r * T;
@@ -818,6 +843,10 @@ __device__ __forceinline__ void band_rowifft_tile(const Batch& bt, const int nc,
         if (x <= RGT || x >= N - H) {
           wa[wi] = w[r][q].x;
           if (hasb) wb[wi] = w[r][q].y;
+          if (wi >= 5 && wi < BX - 5) {
+            if (pa) best = fmaxf(best, w[r][q].x);
+            if (pb) best = fmaxf(best, w[r][q].y);
+          }
         }
       };
       if (narrow) {
@@ -831,6 +860,10 @@ __device__ __forceinline__ void band_rowifft_tile(const Batch& bt, const int nc,
       }
     }
   }
+  best = wave_max(best);
+  constexpr int W = T / 64;
+  static_assert(W == row_waves(N), "one value per wave");
+  if ((tid & 63) == 0) bt.peak_part[((size_t)ci * bt.shape.band_pairs() + p) * W + (tid >> 6)] = best;
 }
 
 template <int N, int T>
@@ -849,65 +882,91 @@ __global__ __launch_bounds__(T) void k_band_rowifft_dyn(Batch bt) {
 
 // ---------------------------------------------------------------------------
 
-// PCE of candidate ci.
+// PCE of candidate ci.  Three dependent rounds of loads: the partial results of the other
+// kernels, all requested together; the two rows that hold the peak (its first place in
+// row-major order: the first row pair that reaches the largest value, and the first such
+// value in it); the exclusion block around it.  Bound by their latency: 6 us in a small
+// launch (14 us when it scanned the whole window, and 224 instead of 8 us for 384
+// candidates of 720p frames in a 1080p fingerprint).
 template <int T>
 __device__ __forceinline__ void pce_tile(const Batch& bt, const int ci) {
-  __shared__ double red[(T + 63) / 64];
-  __shared__ float sbest[(T + 63) / 64];
-  __shared__ int sidx[(T + 63) / 64];
-  __shared__ int peak_idx;
-  // peak search over SY x SX shifts (-R..ey+R by -R..ex+R), in a window of BR x BX
+  constexpr int W = T / 64;
+  constexpr int kNone = 0x7fffffff;
+  __shared__ double red[W], rede[W], reds1[W], reds2[W];
+  __shared__ float smax[W];
+  __shared__ int spair[W], sidx[W];
   const int R = bt.shape.radius, BR = bt.shape.band_rows(), BX = bt.shape.win_cols();
-  const int SY = bt.shape.ey + 2 * R + 1, SX = bt.shape.ex + 2 * R + 1, SS = SY * SX;
+  const int SX = BX - 10;  // the peak is sought over (BR - 10) x SX shifts (-R..ey+R by -R..ex+R)
   const float* w = bt.win + (size_t)ci * BR * BX;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int rw = row_waves(bt.shape.N), bp = peak_parts(bt.shape), nstrips = col_blocks(bt.shape),
+            np = bt.shape.row_pairs();
   float best = -INFINITY;
-  int bidx = 0x7fffffff;
-  constexpr int G = 16;  // window values loaded per thread before they are compared
-  for (int base = 0; base < SS; base += G * T) {
-    float v[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int idx = base + threadIdx.x + g * T;
-      const int r = idx / SX, c = idx % SX;
-      v[g] = idx < SS ? w[(r + 5) * BX + (c + 5)] : -INFINITY;
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int idx = base + threadIdx.x + g * T;
-      if (idx < SS && v[g] > best) {  // indices increase per thread: the first maximum is kept
-        best = v[g];
-        bidx = idx;
-      }
+  int pair = kNone;
+  for (int i = threadIdx.x; i < bp; i += T) {
+    const float v = bt.peak_part[(size_t)ci * bp + i];
+    if (v > best) {  // indices increase per thread: the first maximum is kept
+      best = v;
+      pair = i / rw;
     }
   }
+  double e = 0.0, s1 = 0.0, s2 = 0.0;
+  for (int i = threadIdx.x; i < nstrips; i += T) e += bt.energy_part[(size_t)ci * nstrips + i];
+  for (int i = threadIdx.x; i < np; i += T) {
+    const double2 v = bt.norm_part[(size_t)ci * np + i];
+    s1 += v.x;
+    s2 += v.y;
+  }
+  const float wbest = wave_max(best);
+  if (best < wbest) pair = kNone;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int oi = __shfl_xor(bidx, o, 64);
-    if (ov > best || (ov == best && oi < bidx)) {
-      best = ov;
-      bidx = oi;
+    pair = min(pair, __shfl_xor(pair, o, 64));
+    e += __shfl_xor(e, o, 64);
+    s1 += __shfl_xor(s1, o, 64);
+    s2 += __shfl_xor(s2, o, 64);
+  }
+  if (lane == 0) {
+    smax[wv] = wbest;
+    spair[wv] = pair;
+    rede[wv] = e;
+    reds1[wv] = s1;
+    reds2[wv] = s2;
+  }
+  __syncthreads();
+  best = -INFINITY;
+  pair = kNone;
+  e = s1 = s2 = 0.0;
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    if (smax[i] > best || (smax[i] == best && spair[i] < pair)) {
+      best = smax[i];
+      pair = spair[i];
+    }
+    e += rede[i];
+    s1 += reds1[i];
+    s2 += reds2[i];
+  }
+  // its place in window rows 2 pair and 2 pair + 1 (those in the peak's range)
+  int bidx = kNone;
+  if (pair != kNone) {
+    const int r0 = max(2 * pair, 5), r1 = min(2 * pair + 2, BR - 5), n = (r1 - r0) * SX;
+    for (int i = threadIdx.x; i < n; i += T) {
+      const int r = r0 + (i >= SX ? 1 : 0), c = i >= SX ? i - SX : i;
+      if (w[r * BX + c + 5] == best) {
+        bidx = (r - 5) * SX + c;
+        break;
+      }
     }
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) {
-    sbest[wv] = best;
-    sidx[wv] = bidx;
-  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) bidx = min(bidx, __shfl_xor(bidx, o, 64));
+  if (lane == 0) sidx[wv] = bidx;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < (T + 63) / 64; ++i)
-      if (sbest[i] > best || (sbest[i] == best && sidx[i] < bidx)) {
-        best = sbest[i];
-        bidx = sidx[i];
-      }
-    peak_idx = bidx;
-    sbest[0] = best;
-  }
-  __syncthreads();
-  const int pidx = peak_idx;
-  const bool found = pidx != 0x7fffffff;
-  const int pr = found ? pidx / SX : R, pc = found ? pidx % SX : R;
+#pragma unroll
+  for (int i = 0; i < W; ++i) bidx = min(bidx, sidx[i]);
+  const bool found = bidx != kNone;
+  const int pr = found ? bidx / SX : R, pc = found ? bidx % SX : R;
   // energy of the exclusion block (its centre is at window (pr + 5, pc + 5))
   double sd = 0.0;
   if (threadIdx.x < 121) {
@@ -915,25 +974,12 @@ __device__ __forceinline__ void pce_tile(const Batch& bt, const int ci) {
     const double v = (double)w[(pr + 5 + a) * BX + (pc + 5 + b)];
     sd = v * v;
   }
-  sd = block_sum<T>(sd, red);
-  const int nstrips = col_blocks(bt.shape);
-  double e = 0.0;
-  for (int i = threadIdx.x; i < nstrips; i += T) e += bt.energy_part[(size_t)ci * nstrips + i];
-  e = block_sum<T>(e, red);
-  const int np = bt.shape.row_pairs();
-  double s1 = 0.0, s2 = 0.0;
-  for (int i = threadIdx.x; i < np; i += T) {
-    const double2 v = bt.norm_part[(size_t)ci * np + i];
-    s1 += v.x;
-    s2 += v.y;
-  }
-  s1 = block_sum<T>(s1, red);
-  s2 = block_sum<T>(s2, red);
+  sd = block_sum<T, true>(sd, red);
   if (threadIdx.x == 0) {
     // Both spectra are stored at twice the DFT (row kernel): the window holds 4 MN C and
     // the energies 16 (MN)^2 C^2 (Parseval: 16 MN sum C^2); the divisions are exact.
     const double MN = (double)bt.shape.M * (double)bt.shape.N;
-    const double cpk = (double)sbest[0] / (4.0 * MN);      // C at the peak
+    const double cpk = (double)best / (4.0 * MN);      // C at the peak
     const double all = e / (16.0 * MN);                    // sum over all shifts of C^2 (Parseval)
     const double excl = sd / (16.0 * MN * MN);             // sum over the exclusion block
     const double off = all - excl;
@@ -1032,7 +1078,7 @@ __global__ __launch_bounds__(T) void k_pad_frames(const E* src, int64_t sfs, int
 
 template <int N>
 constexpr int row_threads() {
-  return N >= 3840 ? 256 : (N >= 1280 ? 128 : 64);
+  return 64 * row_waves(N);
 }
 template <int M>
 constexpr int col_threads() {

@@ -84,6 +84,12 @@ __host__ __device__ constexpr inline int col_split(int M) { return M >= 1280 ? 2
 // Column workgroups (and energy partial sums) per candidate.
 __host__ __device__ inline int col_blocks(const Shape& s) { return col_strips(s) * col_split(s.M); }
 
+// Wavefronts of a row transform's workgroup.
+__host__ __device__ constexpr inline int row_waves(int N) { return N >= 3840 ? 4 : (N >= 1280 ? 2 : 1); }
+// Largest window values per candidate: one per band row pair and wavefront of its
+// workgroup.
+__host__ __device__ inline int peak_parts(const Shape& s) { return s.band_pairs() * row_waves(s.N); }
+
 struct Batch {
   Shape shape;
   int nc;                      // candidates in this batch
@@ -101,6 +107,7 @@ struct Batch {
   float* win;                  // [nc][band_rows][win_cols]
   double2* norm_part;          // [nc][row_pairs] (sum r, sum r^2)
   double* energy_part;         // [nc][col_blocks]
+  float* peak_part;            // [nc][band_pairs][row_waves(N)]
   CandRecord* rec;             // [nc]
   const c32* twM;              // twiddles of the column plan (length M)
   const c32* twMi;             // twiddles of the reversed column plan

@@ -257,7 +257,8 @@ int Runner::batch_size(const Shape& sh) const {
 size_t Runner::workspace_bytes(const Shape& sh, int nc) const {
   return (size_t)nc * ((size_t)sh.M * tiled_cols(sh) * sizeof(c32) + (size_t)sh.band_rows() * sh.Nh() * sizeof(c32) +
                        (size_t)sh.band_rows() * sh.win_cols() * sizeof(float) +
-                       (size_t)sh.row_pairs() * sizeof(double2) + (size_t)col_blocks(sh) * sizeof(double));
+                       (size_t)sh.row_pairs() * sizeof(double2) + (size_t)col_blocks(sh) * sizeof(double) +
+                       (size_t)peak_parts(sh) * sizeof(float));
 }
 
 prnu_status Runner::ensure_workspace(const Shape& sh, int nc) {
@@ -266,7 +267,8 @@ prnu_status Runner::ensure_workspace(const Shape& sh, int nc) {
                     (size_t)nc * sh.band_rows() * sh.Nh() * sizeof(c32) > ws_band.cap ||
                     (size_t)nc * sh.band_rows() * sh.win_cols() * sizeof(float) > ws_win.cap ||
                     (size_t)nc * sh.row_pairs() * sizeof(double2) > ws_norm.cap ||
-                    (size_t)nc * col_blocks(sh) * sizeof(double) > ws_energy.cap;
+                    (size_t)nc * col_blocks(sh) * sizeof(double) > ws_energy.cap ||
+                    (size_t)nc * peak_parts(sh) * sizeof(float) > ws_peak.cap;
   // Launches already queued on this stream may still use the buffers about to be
   // replaced: let them finish first.
   if (grow && (e = hipStreamSynchronize(stream)) != hipSuccess)
@@ -275,7 +277,8 @@ prnu_status Runner::ensure_workspace(const Shape& sh, int nc) {
       (e = ws_band.reserve((size_t)nc * sh.band_rows() * sh.Nh() * sizeof(c32))) != hipSuccess ||
       (e = ws_win.reserve((size_t)nc * sh.band_rows() * sh.win_cols() * sizeof(float))) != hipSuccess ||
       (e = ws_norm.reserve((size_t)nc * sh.row_pairs() * sizeof(double2))) != hipSuccess ||
-      (e = ws_energy.reserve((size_t)nc * col_blocks(sh) * sizeof(double))) != hipSuccess)
+      (e = ws_energy.reserve((size_t)nc * col_blocks(sh) * sizeof(double))) != hipSuccess ||
+      (e = ws_peak.reserve((size_t)nc * peak_parts(sh) * sizeof(float))) != hipSuccess)
     return fail(PRNU_E_NOMEM, "workspace: %s", hipGetErrorString(e));
   return PRNU_OK;
 }
@@ -295,6 +298,7 @@ static Batch make_batch(const Runner& r, const Shape& sh, int dtype, const Frame
   b.win = reinterpret_cast<float*>(r.ws_win.ptr);
   b.norm_part = reinterpret_cast<double2*>(r.ws_norm.ptr);
   b.energy_part = reinterpret_cast<double*>(r.ws_energy.ptr);
+  b.peak_part = reinterpret_cast<float*>(r.ws_peak.ptr);
   b.rec = rec + start;
   b.twM = twM;
   b.twMi = twMi;
@@ -348,7 +352,8 @@ prnu_status Runner::run(Context& ctx, const Shape& sh, int dtype, const FrameRef
         (uintptr_t)n,             (uintptr_t)bc,            (uintptr_t)sc.order,       (uintptr_t)frames,
         (uintptr_t)fps,           (uintptr_t)cand,          (uintptr_t)rec,            (uintptr_t)ws_inter.ptr,
         (uintptr_t)ws_band.ptr,   (uintptr_t)ws_win.ptr,    (uintptr_t)ws_norm.ptr,    (uintptr_t)ws_energy.ptr,
-        (uintptr_t)twM,           (uintptr_t)twMi,          (uintptr_t)twN,            (uintptr_t)proj};
+        (uintptr_t)ws_peak.ptr,   (uintptr_t)twM,           (uintptr_t)twMi,          (uintptr_t)twN,
+        (uintptr_t)proj};
     for (GraphEntry& g : graphs)
       if (g.key == key) {
         g.last_use = ++graph_clock;
@@ -1478,9 +1483,10 @@ prnu_status prnu_score_grid_noalloc(prnu_ctx* ctx, prnu_fp fp, const prnu_frames
   const size_t o_ws = o_rec + round256(sizeof(CandRecord) * (size_t)n);
   const size_t b_inter = (size_t)sh.M * tiled_cols(sh) * sizeof(c32), b_band = (size_t)sh.band_rows() * sh.Nh() * sizeof(c32),
                b_win = (size_t)sh.band_rows() * sh.win_cols() * sizeof(float),
-               b_norm = (size_t)sh.row_pairs() * sizeof(double2), b_energy = (size_t)col_blocks(sh) * sizeof(double);
-  const size_t per = b_inter + b_band + b_win + b_norm + b_energy;
-  const size_t slack = 5 * 256;
+               b_norm = (size_t)sh.row_pairs() * sizeof(double2), b_energy = (size_t)col_blocks(sh) * sizeof(double),
+               b_peak = (size_t)peak_parts(sh) * sizeof(float);
+  const size_t per = b_inter + b_band + b_win + b_norm + b_energy + b_peak;
+  const size_t slack = 6 * 256;
   if (o_ws + slack + per > kScratchBytes)
     return fail(PRNU_E_NOMEM, "frame %dx%d against %dx%d needs more than the %zu-byte scratch", frames->height,
                 frames->width, sh.M, sh.N, kScratchBytes);
@@ -1491,6 +1497,7 @@ prnu_status prnu_score_grid_noalloc(prnu_ctx* ctx, prnu_fp fp, const prnu_frames
   float* win = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(band) + round256(b_band * chunk));
   double2* norm = reinterpret_cast<double2*>(reinterpret_cast<unsigned char*>(win) + round256(b_win * chunk));
   double* energy = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(norm) + round256(b_norm * chunk));
+  float* peak = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(energy) + round256(b_energy * chunk));
   hipStream_t s = reinterpret_cast<hipStream_t>(frames->stream);
   // frame table, fingerprint table and the grid's item, written by a kernel from its
   // arguments
@@ -1533,6 +1540,7 @@ prnu_status prnu_score_grid_noalloc(prnu_ctx* ctx, prnu_fp fp, const prnu_frames
     b.win = win;
     b.norm_part = norm;
     b.energy_part = energy;
+    b.peak_part = peak;
     b.rec = rec + start;
     b.twM = twM;
     b.twMi = twMi;

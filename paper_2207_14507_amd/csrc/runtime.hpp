@@ -134,7 +134,7 @@ struct StepDev {
 // that fit its workspace, on one stream.  Optionally records per-kernel HIP events.
 struct Runner {
   hipStream_t stream = nullptr;
-  DevBuf ws_inter, ws_band, ws_win, ws_norm, ws_energy;
+  DevBuf ws_inter, ws_band, ws_win, ws_norm, ws_energy, ws_peak;
   double batch_bytes = 512.0 * 1024 * 1024;
   int batch_override = 0;
   bool prof_on = false;
