@@ -62,6 +62,41 @@ def test_padded_grid_matches_oracle(P, ctx, fp_shape, frame_shape, R):
     P.prnu_close_fingerprint(ctx, fp)
 
 
+@pytest.mark.parametrize("frame_shape,R", [((43, 160), 10), ((44, 158), 10), ((119, 100), 12)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_rows_without_samples(P, ctx, frame_shape, R, bf16):
+    """Row pairs wholly outside the frame's samples: past an odd and an even last row, with
+    and without columns past the last one, and those that scales well below 1 sample
+    beyond its edges; and a NaN in the first row, which reaches every candidate through
+    the samples clamped onto the border above it."""
+    seq = synth.cropped_sequence(34, (120, 160), frame_shape, 1, radius=4)
+    frames, scales, W = seq.frames, None, seq.frames[0]
+    if bf16:
+        b, s = synth.quantize_bf16(W)
+        frames, scales, W = b[None], np.array([s], np.float32), synth.dequantize_bf16(b, s)
+    grid = (7, 0.6, 1.2, 3, -2.0, 2.0)
+    opts = P.make_opts(grid=grid, radius=R)
+    fp = P.prnu_open_fingerprint(ctx, seq.K)
+    cands = O.candidates(O.grid_values(*grid[:3]), O.grid_values(*grid[3:]))
+    pce, rho, dx, dy = P.prnu_score_grid(ctx, fp, frames, 0, opts, scales=scales)
+    o_pce, o_dx, o_dy, o_gap, rs, near = oracle_scores(seq.K, W, cands, R)
+    check_candidates(f"{frame_shape}", pce, dx, dy, o_pce, o_dx, o_dy, o_gap, near)
+    bad = frames.copy()
+    bad[0, 0, 7] = 0x7fc0 if bf16 else np.nan
+    Mf, Nf = frame_shape
+    ux, uy = np.arange(160) - (Nf - 1) / 2, (np.arange(120) - (Mf - 1) / 2)[:, None]
+    past = (np.arange(120)[:, None] >= Mf) | (np.arange(160) >= Nf)
+    touched = []
+    for s, t in cands:
+        c, n = math.cos(math.radians(t)), math.sin(math.radians(t))
+        bx = np.clip((c * ux - n * uy) / s + (Nf - 1) / 2, -1, Nf)
+        by = np.where(past, -1.0, np.clip((n * ux + c * uy) / s + (Mf - 1) / 2, -1, Mf))
+        touched.append(bool(np.any((bx >= 6) & (bx < 8) & (by >= -1) & (by < 1))))
+    got = P.prnu_score_grid(ctx, fp, bad, 0, opts, scales=scales)[0]
+    assert np.array_equal(np.isnan(got), touched), (np.isnan(got), touched)
+    P.prnu_close_fingerprint(ctx, fp)
+
+
 def test_crop_position_and_planted_transform_recovered(P, ctx):
     planted = [synth.Planted(1.015, -0.5, 3, -2), synth.Planted(0.985, 1.0, -4, 5)]
     seq = synth.cropped_sequence(32, (256, 256), (192, 224), 2, planted=planted, offset=(40, 17))
