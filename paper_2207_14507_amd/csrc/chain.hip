@@ -48,13 +48,20 @@ __device__ CandSite gen_site(const GridGen& g, int i) {
   return CandSite{local_node_d(si, g.ns, c.cs, g.lo0), local_node_d(ri, g.nr, c.ct, g.lo1)};
 }
 
-__global__ __launch_bounds__(256) void k_gen(const ItemDesc* items, CandParam* cand, CandSite* site) {
-  const ItemDesc& it = items[blockIdx.x];
-  const int i = (int)blockIdx.y * 256 + (int)threadIdx.x;
-  if (i >= it.n) return;
+// Candidate i of an item into the launch's list.
+__device__ __forceinline__ void gen_candidate(const ItemDesc& it, int i, CandParam* cand, CandSite* site) {
   const CandSite c = gen_site(it.gen, i);
   cand[it.off + i] = param_of(c, it.slot, it.fslot);
   site[it.off + i] = c;
+}
+
+// The launch's candidate list; n_dev (if any), the length of its fallback list, starts
+// from zero.
+__global__ __launch_bounds__(256) void k_gen(const ItemDesc* items, CandParam* cand, CandSite* site, int* n_dev) {
+  if (n_dev && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *n_dev = 0;
+  const ItemDesc& it = items[blockIdx.x];
+  const int i = (int)blockIdx.y * 256 + (int)threadIdx.x;
+  if (i < it.n) gen_candidate(it, i, cand, site);
 }
 
 // x beats the current best (bv, bi): finite comparison in FP64, the lower index on
@@ -152,18 +159,83 @@ __device__ void commit(const ItemDesc& it, const FrameBest& fb) {
   if (it.result) *it.result = r;
 }
 
-// Start phase: one block per item over its segment of the launch's list.  Merge phase:
-// one block per warm item whose fallback grid was searched, over its fallback segment.
+// One block per item over its segment of the launch's list: the item's best, and for a
+// warm item whose local best falls short the fallback grid, which takes the next fb_n
+// places of the fallback list (in any order of the items: a candidate's score does not
+// depend on its place) and is written there by the block.
 template <int T>
 __global__ __launch_bounds__(T) void k_argmax(const ItemDesc* items, ItemOut* outs, const CandRecord* rec,
-                                              const CandSite* site, int merge_fallback, const CandRecord* fb_rec,
-                                              const CandSite* fb_site) {
+                                              const CandSite* site, int* n_dev, CandParam* fb_cand,
+                                              CandSite* fb_site) {
   const ItemDesc& it = items[blockIdx.x];
   ItemOut& out = outs[blockIdx.x];
+  __shared__ int fb_at;  // the fallback grid's first place, or -1
   double bv;
   int bi;
-  if (merge_fallback) {
-    if (it.mode != kModeWarm || !out.need) return;  // uniform per block
+  const CandRecord* r = rec + it.off;
+  const CandSite* c = site + it.off;
+  segment_best<T>(r, it.n, bv, bi);
+  if (threadIdx.x == 0) {
+    FrameBest fb;
+    if (it.mode == kModeRefine && it.merge) {
+      fb = *it.best;
+    } else {
+      fb.index = -1;
+      fb.n_eval = 0;
+      fb.fell_back = 0;
+      fb.pad = 0;
+      fb.s = fb.t = 0.0;
+      fb.rec = CandRecord{};
+    }
+    fold(fb, r, c, bi, fb.n_eval, it.n);
+    int need = 0;
+    if (it.mode == kModeWarm) {
+      if (!it.state->have) {
+        // no earlier frame of the video has a finite result: this frame is searched like
+        // a first frame, on the full grid alone (the local segment does not count)
+        fb.index = -1;
+        fb.n_eval = 0;
+        fb.fell_back = 0;
+        need = 1;
+      } else {
+        // the local best falls short (or nothing finite was scored): the full grid follows
+        need = (bi < 0 || !(r[bi].pce >= it.fallback_pce)) ? 1 : 0;
+        fb.fell_back = need;
+      }
+    }
+    fb_at = need ? atomicAdd(n_dev, it.fb_n) : -1;
+    out.need = need;
+    out.fb_off = need ? fb_at : 0;
+    out.seg_index = bi;
+    out.seg_s = bi >= 0 ? c[bi].s : 0.0;
+    out.seg_t = bi >= 0 ? c[bi].t : 0.0;
+    out.seg_pce = bi >= 0 ? r[bi].pce : 0.0;
+    *it.best = fb;
+    if (!need) commit(it, fb);
+  }
+  if (it.mode != kModeWarm) return;  // uniform per block
+  __syncthreads();
+  if (fb_at < 0) return;
+  for (int i = (int)threadIdx.x; i < it.fb_n; i += T) {
+    const CandSite x = gen_site(it.full, i);
+    fb_cand[fb_at + i] = param_of(x, it.slot, it.fslot);
+    fb_site[fb_at + i] = x;
+  }
+}
+
+// One block per warm item after its fallback grid, if it needed one, was searched: the
+// grid's best folded into the frame's.  With next (one item only), the block then
+// generates the video's next item, whose centre the frame's result has set, in the same
+// launch.
+template <int T>
+__global__ __launch_bounds__(T) void k_merge(const ItemDesc* items, const ItemOut* outs, const CandRecord* fb_rec,
+                                             const CandSite* fb_site, const ItemDesc* next, CandParam* cand,
+                                             CandSite* site, int* n_dev) {
+  const ItemDesc& it = items[blockIdx.x];
+  const ItemOut& out = outs[blockIdx.x];
+  if (it.mode == kModeWarm && out.need) {  // uniform per block
+    double bv;
+    int bi;
     const CandRecord* r = fb_rec + out.fb_off;
     const CandSite* c = fb_site + out.fb_off;
     segment_best<T>(r, it.fb_n, bv, bi);
@@ -173,73 +245,12 @@ __global__ __launch_bounds__(T) void k_argmax(const ItemDesc* items, ItemOut* ou
       *it.best = fb;
       commit(it, fb);
     }
-    return;
   }
-  const CandRecord* r = rec + it.off;
-  const CandSite* c = site + it.off;
-  segment_best<T>(r, it.n, bv, bi);
-  if (threadIdx.x != 0) return;
-  FrameBest fb;
-  if (it.mode == kModeRefine && it.merge) {
-    fb = *it.best;
-  } else {
-    fb.index = -1;
-    fb.n_eval = 0;
-    fb.fell_back = 0;
-    fb.pad = 0;
-    fb.s = fb.t = 0.0;
-    fb.rec = CandRecord{};
-  }
-  fold(fb, r, c, bi, fb.n_eval, it.n);
-  out.need = 0;
-  out.fb_off = 0;
-  out.seg_index = bi;
-  out.seg_s = bi >= 0 ? c[bi].s : 0.0;
-  out.seg_t = bi >= 0 ? c[bi].t : 0.0;
-  out.seg_pce = bi >= 0 ? r[bi].pce : 0.0;
-  if (it.mode == kModeWarm) {
-    if (!it.state->have) {
-      // no earlier frame of the video has a finite result: this frame is searched like
-      // a first frame, on the full grid alone (the local segment does not count)
-      fb.index = -1;
-      fb.n_eval = 0;
-      fb.fell_back = 0;
-      out.need = 1;
-    } else {
-      // the local best falls short (or nothing finite was scored): the full grid follows
-      out.need = (bi < 0 || !(r[bi].pce >= it.fallback_pce)) ? 1 : 0;
-      fb.fell_back = out.need;
-    }
-  }
-  *it.best = fb;
-  if (it.mode != kModeWarm || !out.need) commit(it, fb);
-}
-
-__global__ void k_plan(const ItemDesc* items, int n, ItemOut* outs, int* n_dev) {
-  if (threadIdx.x != 0) return;
-  int total = 0;
-  for (int i = 0; i < n; ++i) {
-    const bool need = items[i].mode == kModeWarm && outs[i].need;
-    outs[i].fb_off = total;
-    if (need) total += items[i].fb_n;
-  }
-  *n_dev = total;
-}
-
-__global__ __launch_bounds__(256) void k_fill(const ItemDesc* items, int n, const ItemOut* outs, const int* n_dev,
-                                              CandParam* fb_cand, CandSite* fb_site) {
-  const int e = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (e >= *n_dev) return;
-  for (int i = 0; i < n; ++i) {
-    const ItemDesc& it = items[i];
-    if (it.mode != kModeWarm || !outs[i].need) continue;
-    const int j = e - outs[i].fb_off;
-    if (j < 0 || j >= it.fb_n) continue;
-    const CandSite c = gen_site(it.full, j);
-    fb_cand[e] = param_of(c, it.slot, it.fslot);
-    fb_site[e] = c;
-    return;
-  }
+  if (!next) return;
+  __syncthreads();  // the state the next item's grid is centred on
+  if (threadIdx.x == 0) *n_dev = 0;
+  const ItemDesc nx = *next;
+  for (int i = (int)threadIdx.x; i < nx.n; i += T) gen_candidate(nx, i, cand, site);
 }
 
 __global__ void k_chain_init(ChainState* st, int has_init, double cs, double ct) {
@@ -265,28 +276,26 @@ __global__ void k_scatter(const CandRecord* rec, int n, double* pce, double* rho
 
 }  // namespace
 
-hipError_t launch_gen(const ItemDesc* items, int n, int max_n, CandParam* cand, CandSite* site, hipStream_t s) {
+hipError_t launch_gen(const ItemDesc* items, int n, int max_n, CandParam* cand, CandSite* site, int* n_dev,
+                      hipStream_t s) {
   if (n <= 0 || max_n <= 0) return hipSuccess;
-  k_gen<<<dim3((unsigned)n, (unsigned)((max_n + 255) / 256)), 256, 0, s>>>(items, cand, site);
+  k_gen<<<dim3((unsigned)n, (unsigned)((max_n + 255) / 256)), 256, 0, s>>>(items, cand, site, n_dev);
   return hipGetLastError();
 }
 
 hipError_t launch_argmax(const ItemDesc* items, int n, ItemOut* outs, const CandRecord* rec, const CandSite* site,
-                         bool merge_fallback, const CandRecord* fb_rec, const CandSite* fb_site, hipStream_t s) {
+                         int* n_dev, CandParam* fb_cand, CandSite* fb_site, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  k_argmax<256><<<dim3((unsigned)n), 256, 0, s>>>(items, outs, rec, site, merge_fallback ? 1 : 0, fb_rec, fb_site);
+  k_argmax<256><<<dim3((unsigned)n), 256, 0, s>>>(items, outs, rec, site, n_dev, fb_cand, fb_site);
   return hipGetLastError();
 }
 
-hipError_t launch_plan(const ItemDesc* items, int n, ItemOut* outs, int* n_dev, hipStream_t s) {
-  k_plan<<<1, 64, 0, s>>>(items, n, outs, n_dev);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill(const ItemDesc* items, int n, const ItemOut* outs, const int* n_dev, int max_fb,
-                       CandParam* fb_cand, CandSite* fb_site, hipStream_t s) {
-  if (max_fb <= 0) return hipSuccess;
-  k_fill<<<dim3((unsigned)((max_fb + 255) / 256)), 256, 0, s>>>(items, n, outs, n_dev, fb_cand, fb_site);
+hipError_t launch_merge(const ItemDesc* items, int n, const ItemOut* outs, const CandRecord* fb_rec,
+                        const CandSite* fb_site, const ItemDesc* next, CandParam* cand, CandSite* site, int* n_dev,
+                        hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  if (next && n != 1) return hipErrorInvalidValue;
+  k_merge<256><<<dim3((unsigned)n), 256, 0, s>>>(items, outs, fb_rec, fb_site, next, cand, site, n_dev);
   return hipGetLastError();
 }
 

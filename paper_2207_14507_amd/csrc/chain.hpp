@@ -9,14 +9,14 @@
 //   k_argmax     reduces each item's records to its best candidate (FP64 compare,
 //                lowest index on ties, NaN never wins), folds it into the frame's
 //                running best and, for a warm frame, decides on the device whether
-//                the full grid must follow (local best below the fallback level);
-//   k_plan       lays the fallback grids of the items that need one end to end and
-//                writes their total, which sizes the device-counted launch set that
-//                searches them;
-//   k_fill       writes those fallback candidates;
-//   k_argmax     (merge phase) folds each fallback segment into its frame's best
-//                (earlier candidates win ties) and commits the frame: its result
-//                record and the centre of the video's next local grid.
+//                the full grid must follow (local best below the fallback level); the
+//                grids that must are counted and written end to end into the fallback
+//                list, whose length sizes the device-counted launch set that searches
+//                them;
+//   k_merge      folds each fallback segment into its frame's best (earlier candidates
+//                win ties) and commits the frame: its result record and the centre of
+//                the video's next local grid; in a chain of single items it generates
+//                that grid too.
 // No host round trip is needed between the frames of a chained video.
 #pragma once
 
@@ -97,12 +97,17 @@ struct ItemOut {
 // Device helpers of the launches above (chain.hip).  items/outs: device arrays of n
 // items; cand/site: the launch's candidate list; rec its records; fb_* the fallback
 // list (max_fb entries) and n_dev its device-written length.
-hipError_t launch_gen(const ItemDesc* items, int n, int max_n, CandParam* cand, CandSite* site, hipStream_t s);
+// launch_gen also sets n_dev (may be null) to zero, launch_argmax counts and writes the
+// fallback list (max_fb entries) of the warm items that need their full grid, launch_merge
+// folds the searched fallback grids in and, for a launch of one item, can generate the
+// video's next item (next, else null) as launch_gen would.
+hipError_t launch_gen(const ItemDesc* items, int n, int max_n, CandParam* cand, CandSite* site, int* n_dev,
+                      hipStream_t s);
 hipError_t launch_argmax(const ItemDesc* items, int n, ItemOut* outs, const CandRecord* rec, const CandSite* site,
-                         bool merge_fallback, const CandRecord* fb_rec, const CandSite* fb_site, hipStream_t s);
-hipError_t launch_plan(const ItemDesc* items, int n, ItemOut* outs, int* n_dev, hipStream_t s);
-hipError_t launch_fill(const ItemDesc* items, int n, const ItemOut* outs, const int* n_dev, int max_fb,
-                       CandParam* fb_cand, CandSite* fb_site, hipStream_t s);
+                         int* n_dev, CandParam* fb_cand, CandSite* fb_site, hipStream_t s);
+hipError_t launch_merge(const ItemDesc* items, int n, const ItemOut* outs, const CandRecord* fb_rec,
+                        const CandSite* fb_site, const ItemDesc* next, CandParam* cand, CandSite* site, int* n_dev,
+                        hipStream_t s);
 // Device state of a chained video before its first frame: the caller's initial
 // transform, or no centre (a warm item whose video has no centre yet is searched on its
 // full grid alone, like a first frame).

@@ -429,7 +429,14 @@ prnu_status Runner::run_dyn(Context& ctx, const Shape& sh, int dtype, const Fram
   Schedule sc;
   prnu_status st = ctx.schedule(sh, dtype, *this, sc);
   if (st != PRNU_OK) return st;
-  if (batch_override > 0) sc.chunk = batch_override;
+  if (batch_override > 0) {
+    sc.chunk = batch_override;
+  } else if (n_max > sc.chunk && n_max <= 2 * sc.chunk && workspace_bytes(sh, n_max) <= ctx.tune_cap_bytes) {
+    // Every chunk is four launches whether it holds work or not (about 25 us when it does
+    // not): a list somewhat longer than a batch is one chunk where the workspace limit
+    // and the memory left allow (the full grid's 861 candidates against batches of 768).
+    if (ensure_workspace(sh, n_max) == PRNU_OK) sc.chunk = n_max;
+  }
   if ((st = ensure_workspace(sh, std::min(sc.chunk, n_max))) != PRNU_OK) return st;
   const c32* twM = ctx.twiddles(kColPlan, sh.M);
   const c32* twMi = ctx.twiddles(kColPlanRev, sh.M);
@@ -452,19 +459,18 @@ prnu_status Runner::run_dyn(Context& ctx, const Shape& sh, int dtype, const Fram
 prnu_status Runner::step(Context& ctx, const Shape& sh, int dtype, const FrameRef* frames, const FpRef* fps,
                          const StepDev& d) {
   hipError_t e;
-  if ((e = launch_gen(d.items, d.n_items, d.max_n, d.cand, d.site, stream)) != hipSuccess)
+  if (!d.generated &&
+      (e = launch_gen(d.items, d.n_items, d.max_n, d.cand, d.site, d.n_dev, stream)) != hipSuccess)
     return ctx.hip_fail(e, "candidate generation");
   prnu_status st = run(ctx, sh, dtype, frames, fps, d.cand, d.rec, d.n_total);
   if (st != PRNU_OK) return st;
-  if ((e = launch_argmax(d.items, d.n_items, d.outs, d.rec, d.site, false, nullptr, nullptr, stream)) != hipSuccess)
+  if ((e = launch_argmax(d.items, d.n_items, d.outs, d.rec, d.site, d.n_dev, d.fb_cand, d.fb_site, stream)) !=
+      hipSuccess)
     return ctx.hip_fail(e, "argmax");
   if (d.max_fb <= 0) return PRNU_OK;
-  if ((e = launch_plan(d.items, d.n_items, d.outs, d.n_dev, stream)) != hipSuccess ||
-      (e = launch_fill(d.items, d.n_items, d.outs, d.n_dev, d.max_fb, d.fb_cand, d.fb_site, stream)) != hipSuccess)
-    return ctx.hip_fail(e, "fallback plan");
   if ((st = run_dyn(ctx, sh, dtype, frames, fps, d.fb_cand, d.fb_rec, d.max_fb, d.n_dev, d.fb_expect)) != PRNU_OK)
     return st;
-  if ((e = launch_argmax(d.items, d.n_items, d.outs, nullptr, nullptr, true, d.fb_rec, d.fb_site, stream)) !=
+  if ((e = launch_merge(d.items, d.n_items, d.outs, d.fb_rec, d.fb_site, d.next, d.cand, d.site, d.n_dev, stream)) !=
       hipSuccess)
     return ctx.hip_fail(e, "argmax");
   return PRNU_OK;
@@ -1137,6 +1143,10 @@ prnu_status Context::search(const Fingerprint& fp, const prnu_frames* fr, const 
       df.n_items = 1;
       df.n_total = df.max_n = hi[f].n;
       df.max_fb = hi[f].mode == kModeWarm ? nf : 0;
+      // a warm frame's last launch also generates the next frame's local grid (one block:
+      // grids larger than a few per thread keep a launch of their own)
+      df.generated = f > 0 && hi[f - 1].mode == kModeWarm && nl <= kMergeGen;
+      df.next = hi[f].mode == kModeWarm && f + 1 < F && nl <= kMergeGen ? d.items + f + 1 : nullptr;
       if ((st = runner.step(*this, sh, fr->dtype, frefs, fprefs, df)) != PRNU_OK) return st;
     }
   }
@@ -1160,7 +1170,7 @@ prnu_status Context::score_full(const Shape& sh, int dtype, const prnu_grid& g, 
   hipStream_t s = runner.stream;
   if ((e = hipMemcpyAsync(dev_items.ptr, host_items.ptr, sizeof(ItemDesc), hipMemcpyHostToDevice, s)) != hipSuccess ||
       (e = launch_gen(reinterpret_cast<const ItemDesc*>(dev_items.ptr), 1, n, reinterpret_cast<CandParam*>(dev_cand.ptr),
-                      reinterpret_cast<CandSite*>(dev_site.ptr), s)) != hipSuccess)
+                      reinterpret_cast<CandSite*>(dev_site.ptr), nullptr, s)) != hipSuccess)
     return hip_fail(e, "candidate generation");
   if ((st = runner.run(*this, sh, dtype, reinterpret_cast<FrameRef*>(dev_frefs.ptr),
                        reinterpret_cast<FpRef*>(dev_fprefs.ptr), reinterpret_cast<CandParam*>(dev_cand.ptr),
@@ -1525,7 +1535,7 @@ prnu_status prnu_score_grid_noalloc(prnu_ctx* ctx, prnu_fp fp, const prnu_frames
   if ((e = launch_put(blob, base, s)) != hipSuccess ||
       (e = launch_pad_frames(src, (int)esz, frames->frame_stride, frames->row_stride, 1, sh.Mf(), sh.Nf(),
                              base + o_frame, s)) != hipSuccess ||
-      (e = launch_gen(ditem, 1, n, cand, reinterpret_cast<CandSite*>(base + o_site), s)) != hipSuccess)
+      (e = launch_gen(ditem, 1, n, cand, reinterpret_cast<CandSite*>(base + o_site), nullptr, s)) != hipSuccess)
     return c->hip_fail(e, "allocation-free scoring");
   for (int start = 0; start < n; start += chunk) {
     Batch b{};

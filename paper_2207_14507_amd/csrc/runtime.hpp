@@ -128,7 +128,13 @@ struct StepDev {
   // fallback candidates expected (from the items' previous frames): the chunks that
   // start below this are launched one workgroup per tile
   int fb_expect = 0;
+  // the candidate list was generated by the previous step's last launch; the item that
+  // this step's last launch generates (one-item steps of a chain), or null
+  bool generated = false;
+  const ItemDesc* next = nullptr;
 };
+// Largest next item a merge launch's single block generates.
+constexpr int kMergeGen = 2048;
 
 // Launches the search kernels over candidate arrays already on the device, in chunks
 // that fit its workspace, on one stream.  Optionally records per-kernel HIP events.
