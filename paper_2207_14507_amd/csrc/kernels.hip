@@ -1059,39 +1059,35 @@ __global__ __launch_bounds__(T) void k_pce_dyn(Batch bt) {
 // ---------------------------------------------------------------------------
 // Fingerprint preparation.
 
+// Row sums of K.
 template <int T>
-__global__ __launch_bounds__(T) void k_fp_rowsums(const float* K, int64_t rs, int M, int N, const double* mean,
-                                                  double* part) {
+__global__ __launch_bounds__(T) void k_fp_rowsums(const float* K, int64_t rs, int M, int N, double* part) {
   __shared__ double red[(T + 63) / 64];
   const int y = blockIdx.x;
-  const double mu = mean ? *mean : 0.0;
   double s = 0.0;
-  for (int x = threadIdx.x; x < N; x += T) {
-    const double v = (double)K[(int64_t)y * rs + x] - mu;
-    s += mean ? v * v : v;
-  }
+  for (int x = threadIdx.x; x < N; x += T) s += (double)K[(int64_t)y * rs + x];
   s = block_sum<T>(s, red);
   if (threadIdx.x == 0) part[y] = s;
 }
 
+// K - mean into the staged layout (one block per row of entries), and the row's sum of
+// (K - mean)^2 to part2.  Every block forms the mean from the M row sums itself (17 kB at
+// most, from L2), in one order: a launch of its own for it costs more.
 template <int T>
-__global__ __launch_bounds__(T) void k_fp_finish(const double* part, int M, double count, double* out, int second) {
+__global__ __launch_bounds__(T) void k_fp_center(const float* K, int64_t rs, int M, int N, double count,
+                                                 const double* part, double* part2, double* mean, float* out) {
   __shared__ double red[(T + 63) / 64];
+  __shared__ double smean;
   double s = 0.0;
   for (int i = threadIdx.x; i < M; i += T) s += part[i];
   s = block_sum<T>(s, red);
   if (threadIdx.x == 0) {
-    if (!second) out[0] = s / count;  // mean
-    else out[1] = sqrt(s);            // norm of K - mean
+    smean = s / count;
+    if (blockIdx.x == 0) *mean = smean;
   }
-}
-
-// K - mean into the staged layout (one block per row of entries).
-template <int T>
-__global__ __launch_bounds__(T) void k_fp_center(const float* K, int64_t rs, int M, int N, const double* mean,
-                                                 float* out) {
+  __syncthreads();
+  const double mu = smean;
   const int y0 = (int)blockIdx.x - kBorder, y1 = y0 + 1;
-  const double mu = *mean;
   const int64_t np = padded_row(N);
   float* row = out + (int64_t)blockIdx.x * np * 2;
   for (int x = (int)threadIdx.x - kBorder; x < N + kBorder; x += T) {
@@ -1100,6 +1096,24 @@ __global__ __launch_bounds__(T) void k_fp_center(const float* K, int64_t rs, int
     row[2 * (x + kBorder)] = in0 ? (float)((double)K[(int64_t)y0 * rs + x] - mu) : 0.f;
     row[2 * (x + kBorder) + 1] = in1 ? (float)((double)K[(int64_t)y1 * rs + x] - mu) : 0.f;
   }
+  if (y0 < 0 || y0 >= M) return;
+  double q = 0.0;
+  for (int x = threadIdx.x; x < N; x += T) {
+    const double v = (double)K[(int64_t)y0 * rs + x] - mu;
+    q += v * v;
+  }
+  q = block_sum<T>(q, red);
+  if (threadIdx.x == 0) part2[y0] = q;
+}
+
+// Norm of K - mean from the rows' sums of squares.
+template <int T>
+__global__ __launch_bounds__(T) void k_fp_norm(const double* part2, int M, double* norm) {
+  __shared__ double red[(T + 63) / 64];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < M; i += T) s += part2[i];
+  s = block_sum<T>(s, red);
+  if (threadIdx.x == 0) *norm = sqrt(s);
 }
 
 // Frames into the staged layout (one block per row of entries of one frame).
@@ -1289,11 +1303,10 @@ hipError_t launch_fp_prepare(const float* K, int64_t row_stride, const Shape& sh
                              double* sums, double* stats_out, c32* FK, const c32* twM, const c32* twMi, const c32* twN,
                              const CandParam* ident, const FrameRef* wref, hipStream_t s) {
   const int M = sh.M, N = sh.N;
-  k_fp_rowsums<256><<<M, 256, 0, s>>>(K, row_stride, M, N, nullptr, sums);
-  k_fp_finish<256><<<1, 256, 0, s>>>(sums, M, (double)M * N, stats_out, 0);
-  k_fp_rowsums<256><<<M, 256, 0, s>>>(K, row_stride, M, N, stats_out, sums);
-  k_fp_finish<256><<<1, 256, 0, s>>>(sums, M, (double)M * N, stats_out, 1);
-  k_fp_center<256><<<(unsigned)pair_rows(M), 256, 0, s>>>(K, row_stride, M, N, stats_out, work);
+  double* sums2 = sums + M + 2;
+  k_fp_rowsums<256><<<M, 256, 0, s>>>(K, row_stride, M, N, sums);
+  k_fp_center<256><<<(unsigned)pair_rows(M), 256, 0, s>>>(K, row_stride, M, N, (double)M * N, sums, sums2, stats_out, work);
+  k_fp_norm<256><<<1, 256, 0, s>>>(sums2, M, stats_out + 1);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   Batch b{};

@@ -161,7 +161,7 @@ hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L
 // Fingerprint preparation: FP64 sums of K, K - mean, 2-D DFT into FK (packed).
 // work: device scratch of at least padded_frame(M, N) floats (K - mean in the staged
 // layout); inter: [M][Nh] complex scratch;
-// sums: device double[M + 2]; stats_out: device double[2] (mean, norm); ident: device
+// sums: device double[2 (M + 2)]; stats_out: device double[2] (mean, norm); ident: device
 // candidate {1, 0, 0, 0}; wref: device FrameRef {work, null}.
 hipError_t launch_fp_prepare(const float* K, int64_t row_stride, const Shape& sh, float* work,
                              c32* inter, double* sums, double* stats_out, c32* FK,

@@ -734,15 +734,61 @@ bool Context::get_fp(prnu_fp h, Fingerprint& out) {
 // caller stream is the legacy default stream (torch's default stream), which the
 // library's non-blocking streams do not synchronise with by themselves.
 static prnu_status order_after(Context& ctx, hipStream_t s, void* caller) {
-  hipEvent_t ev;
+  hipEvent_t ev = nullptr;
   hipError_t e;
-  if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return ctx.hip_fail(e, "event create");
+  {
+    std::lock_guard<std::mutex> lk(ctx.ev_mu);
+    if (!ctx.ev_spare.empty()) {
+      ev = ctx.ev_spare.back();
+      ctx.ev_spare.pop_back();
+    }
+  }
+  if (!ev && (e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess)
+    return ctx.hip_fail(e, "event create");
   if ((e = hipEventRecord(ev, (hipStream_t)caller)) != hipSuccess || (e = hipStreamWaitEvent(s, ev, 0)) != hipSuccess) {
     (void)hipEventDestroy(ev);
     return ctx.hip_fail(e, "stream ordering");
   }
-  (void)hipEventDestroy(ev);
+  // the wait holds the event's state as recorded: the next call may record it again
+  std::lock_guard<std::mutex> lk(ctx.ev_mu);
+  ctx.ev_spare.push_back(ev);
   return PRNU_OK;
+}
+
+hipError_t Context::upload(void* dst, const void* host, size_t n) {
+  if (n > (size_t)kBlobBytes) return hipMemcpyAsync(dst, host, n, hipMemcpyHostToDevice, runner.stream);
+  Blob blob;
+  std::memcpy(blob.b, host, n);
+  blob.n = (int32_t)n;
+  return launch_put(blob, dst, runner.stream);
+}
+
+void* Context::alloc_spectrum(size_t bytes, hipError_t* err) {
+  std::lock_guard<std::mutex> lk(fp_mu);
+  for (size_t i = 0; i < fk_spare.size(); ++i)
+    if (fk_spare[i].second == bytes) {
+      void* p = fk_spare[i].first;
+      fk_spare.erase(fk_spare.begin() + (long)i);
+      *err = hipSuccess;
+      return p;
+    }
+  void* p = nullptr;
+  if ((*err = hipMalloc(&p, bytes)) == hipSuccess) return p;
+  if (fk_spare.empty()) return nullptr;
+  // give the spare spectra back and try again
+  for (auto& x : fk_spare) (void)hipFree(x.first);
+  fk_spare.clear();
+  (void)hipGetLastError();
+  return (*err = hipMalloc(&p, bytes)) == hipSuccess ? p : nullptr;
+}
+
+void Context::free_spectrum(void* p, size_t bytes) {
+  size_t held = 0;
+  for (auto& x : fk_spare) held += x.second;
+  if (held + bytes <= kMaxSpectra)
+    fk_spare.emplace_back(p, bytes);
+  else
+    (void)hipFree(p);
 }
 
 // F host frames of M x N elements of esz bytes (frame and row strides in elements) into
@@ -846,18 +892,19 @@ prnu_status Context::stage_frames(const prnu_frames* fr, std::vector<FrameRef>& 
 }
 
 prnu_status Context::upload_refs(const std::vector<FrameRef>& frames, const Fingerprint& fp) {
+  // the frame table and, behind it, the fingerprint's entry
   const size_t fb = sizeof(FrameRef) * std::max<size_t>(1, frames.size());
   hipError_t e;
-  if ((e = host_refs.reserve(fb + sizeof(FpRef))) != hipSuccess || (e = dev_frefs.reserve(fb)) != hipSuccess ||
-      (e = dev_fprefs.reserve(sizeof(FpRef))) != hipSuccess)
+  if ((e = host_refs.reserve(fb + sizeof(FpRef))) != hipSuccess || (e = dev_frefs.reserve(fb + sizeof(FpRef))) != hipSuccess)
     return fail(PRNU_E_NOMEM, "frame tables");
   char* h = reinterpret_cast<char*>(host_refs.ptr);
-  if (!frames.empty()) std::memcpy(h, frames.data(), sizeof(FrameRef) * frames.size());
+  if (frames.empty()) std::memset(h, 0, fb);
+  else std::memcpy(h, frames.data(), fb);
   const FpRef fr{fp.FK, fp.norm};
   std::memcpy(h + fb, &fr, sizeof(fr));
-  if ((e = hipMemcpyAsync(dev_frefs.ptr, h, fb, hipMemcpyHostToDevice, runner.stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(dev_fprefs.ptr, h + fb, sizeof(FpRef), hipMemcpyHostToDevice, runner.stream)) != hipSuccess)
-    return hip_fail(e, "frame tables");
+  static_assert(sizeof(FrameRef) % alignof(FpRef) == 0, "the fingerprint's entry is aligned");
+  dev_fprefs = reinterpret_cast<FpRef*>(reinterpret_cast<char*>(dev_frefs.ptr) + fb);
+  if ((e = upload(dev_frefs.ptr, h, fb + sizeof(FpRef))) != hipSuccess) return hip_fail(e, "frame tables");
   return PRNU_OK;
 }
 
@@ -869,24 +916,23 @@ prnu_status Context::evaluate(const Shape& sh, int dtype, const std::vector<Cand
   recs.assign((size_t)n, CandRecord{});
   if (n == 0) return PRNU_OK;
   hipError_t e;
-  if ((e = host_cand.reserve(sizeof(CandParam) * (size_t)n)) != hipSuccess) return fail(PRNU_E_NOMEM, "pinned");
+  const size_t cb = sizeof(CandParam) * (size_t)n, pb = proj ? sizeof(float) * proj->size() : 0;
+  if ((e = host_cand.reserve(cb + pb)) != hipSuccess) return fail(PRNU_E_NOMEM, "pinned");
   if ((e = host_rec.reserve(sizeof(CandRecord) * (size_t)n)) != hipSuccess) return fail(PRNU_E_NOMEM, "pinned");
   if ((e = dev_cand.reserve(sizeof(CandParam) * (size_t)n)) != hipSuccess) return fail(PRNU_E_NOMEM, "candidates");
   if ((e = dev_rec.reserve(sizeof(CandRecord) * (size_t)n)) != hipSuccess) return fail(PRNU_E_NOMEM, "records");
-  std::memcpy(host_cand.ptr, params.data(), sizeof(CandParam) * (size_t)n);
-  if ((e = hipMemcpyAsync(dev_cand.ptr, host_cand.ptr, sizeof(CandParam) * (size_t)n, hipMemcpyHostToDevice,
-                          runner.stream)) != hipSuccess)
-    return hip_fail(e, "candidate upload");
+  std::memcpy(host_cand.ptr, params.data(), cb);
+  if ((e = upload(dev_cand.ptr, host_cand.ptr, cb)) != hipSuccess) return hip_fail(e, "candidate upload");
   const float* dproj = nullptr;
   if (proj) {
-    if ((e = dev_proj.reserve(sizeof(float) * proj->size())) != hipSuccess) return fail(PRNU_E_NOMEM, "transforms");
-    if ((e = hipMemcpyAsync(dev_proj.ptr, proj->data(), sizeof(float) * proj->size(), hipMemcpyHostToDevice,
-                            runner.stream)) != hipSuccess)
-      return hip_fail(e, "transform upload");
+    if ((e = dev_proj.reserve(pb)) != hipSuccess) return fail(PRNU_E_NOMEM, "transforms");
+    char* hp = reinterpret_cast<char*>(host_cand.ptr) + cb;
+    std::memcpy(hp, proj->data(), pb);
+    if ((e = upload(dev_proj.ptr, hp, pb)) != hipSuccess) return hip_fail(e, "transform upload");
     dproj = reinterpret_cast<const float*>(dev_proj.ptr);
   }
   prnu_status st = runner.run(*this, sh, dtype, reinterpret_cast<FrameRef*>(dev_frefs.ptr),
-                              reinterpret_cast<FpRef*>(dev_fprefs.ptr), reinterpret_cast<CandParam*>(dev_cand.ptr),
+                              dev_fprefs, reinterpret_cast<CandParam*>(dev_cand.ptr),
                               reinterpret_cast<CandRecord*>(dev_rec.ptr), n, dproj);
   if (st != PRNU_OK) return st;
   if ((e = hipMemcpyAsync(host_rec.ptr, dev_rec.ptr, sizeof(CandRecord) * (size_t)n, hipMemcpyDeviceToHost,
@@ -1010,8 +1056,7 @@ prnu_status Context::refine(const Shape& sh, int dtype, int F, const prnu_search
     }
     std::memcpy(host_items.ptr, items.data(), sizeof(ItemDesc) * (size_t)ni);
     std::memcpy(host_lists.ptr, sites.data(), sizeof(CandSite) * (size_t)nt);
-    if ((e = hipMemcpyAsync(dev_items.ptr, host_items.ptr, sizeof(ItemDesc) * (size_t)ni, hipMemcpyHostToDevice, s)) !=
-            hipSuccess ||
+    if ((e = upload(dev_items.ptr, host_items.ptr, sizeof(ItemDesc) * (size_t)ni)) != hipSuccess ||
         (e = hipMemcpyAsync(dev_lists.ptr, host_lists.ptr, sizeof(CandSite) * (size_t)nt, hipMemcpyHostToDevice, s)) !=
             hipSuccess)
       return hip_fail(e, "refinement upload");
@@ -1020,7 +1065,7 @@ prnu_status Context::refine(const Shape& sh, int dtype, int F, const prnu_search
     d.n_total = nt;
     d.max_n = max_n;
     if ((st = runner.step(*this, sh, dtype, reinterpret_cast<FrameRef*>(dev_frefs.ptr),
-                          reinterpret_cast<FpRef*>(dev_fprefs.ptr), d)) != PRNU_OK)
+                          dev_fprefs, d)) != PRNU_OK)
       return st;
     if ((e = hipMemcpyAsync(host_outs.ptr, dev_outs.ptr, sizeof(ItemOut) * (size_t)ni, hipMemcpyDeviceToHost, s)) !=
             hipSuccess ||
@@ -1119,11 +1164,10 @@ prnu_status Context::search(const Fingerprint& fp, const prnu_frames* fr, const 
   }
   hipError_t e;
   hipStream_t s = runner.stream;
-  if ((e = hipMemcpyAsync(dev_items.ptr, host_items.ptr, sizeof(ItemDesc) * (size_t)F, hipMemcpyHostToDevice, s)) !=
-      hipSuccess)
+  if ((e = upload(dev_items.ptr, host_items.ptr, sizeof(ItemDesc) * (size_t)F)) != hipSuccess)
     return hip_fail(e, "item upload");
   const FrameRef* frefs = reinterpret_cast<FrameRef*>(dev_frefs.ptr);
-  const FpRef* fprefs = reinterpret_cast<FpRef*>(dev_fprefs.ptr);
+  const FpRef* fprefs = dev_fprefs;
   StepDev d = sync_step(*this);
   if (!warm) {
     d.n_items = F;
@@ -1168,12 +1212,12 @@ prnu_status Context::score_full(const Shape& sh, int dtype, const prnu_grid& g, 
   *reinterpret_cast<ItemDesc*>(host_items.ptr) = it;
   hipError_t e;
   hipStream_t s = runner.stream;
-  if ((e = hipMemcpyAsync(dev_items.ptr, host_items.ptr, sizeof(ItemDesc), hipMemcpyHostToDevice, s)) != hipSuccess ||
+  if ((e = upload(dev_items.ptr, host_items.ptr, sizeof(ItemDesc))) != hipSuccess ||
       (e = launch_gen(reinterpret_cast<const ItemDesc*>(dev_items.ptr), 1, n, reinterpret_cast<CandParam*>(dev_cand.ptr),
                       reinterpret_cast<CandSite*>(dev_site.ptr), nullptr, s)) != hipSuccess)
     return hip_fail(e, "candidate generation");
   if ((st = runner.run(*this, sh, dtype, reinterpret_cast<FrameRef*>(dev_frefs.ptr),
-                       reinterpret_cast<FpRef*>(dev_fprefs.ptr), reinterpret_cast<CandParam*>(dev_cand.ptr),
+                       dev_fprefs, reinterpret_cast<CandParam*>(dev_cand.ptr),
                        reinterpret_cast<CandRecord*>(dev_rec.ptr), n)) != PRNU_OK)
     return st;
   if ((e = hipMemcpyAsync(host_rec.ptr, dev_rec.ptr, sizeof(CandRecord) * (size_t)n, hipMemcpyDeviceToHost, s)) !=
@@ -1230,6 +1274,8 @@ Context::~Context() {
   shutdown_serving();
   for (auto& kv : tw) (void)hipFree(kv.second);
   for (auto& kv : fps) (void)hipFree(kv.second.FK);
+  for (auto& x : fk_spare) (void)hipFree(x.first);
+  for (hipEvent_t ev : ev_spare) (void)hipEventDestroy(ev);
   if (runner.stream) (void)hipStreamDestroy(runner.stream);
 }
 
@@ -1335,47 +1381,51 @@ prnu_status prnu_open_fingerprint(prnu_ctx* ctx, const float* K, int32_t height,
   const c32* twMi = c->twiddles(kColPlanRev, height);
   const c32* twN = c->twiddles(kRowPlan, width);
   if (!twM || !twMi || !twN) return c->hip_fail(hipErrorOutOfMemory, "twiddle tables");
-  DevBuf kdev, work, inter, sums, stats, small;
+  // Scratch shared with the synchronous searches (same stream, same lock): the upload and
+  // staging buffers of frames, and the search workspace's intermediate.
   const float* Kd = K;
   int64_t rs = row_stride;
   if (on_device) {
     // order after the caller's stream (null: the legacy default stream)
     if ((st = order_after(*c, s, stream)) != PRNU_OK) return st;
   } else {
-    if ((e = kdev.reserve((size_t)height * width * sizeof(float))) != hipSuccess)
+    if ((e = c->stage_tight.reserve((size_t)height * width * sizeof(float))) != hipSuccess)
       return fail(PRNU_E_NOMEM, "fingerprint upload");
-    if ((e = hipMemcpy2DAsync(kdev.ptr, (size_t)width * 4, K, (size_t)row_stride * 4, (size_t)width * 4,
+    if ((e = hipMemcpy2DAsync(c->stage_tight.ptr, (size_t)width * 4, K, (size_t)row_stride * 4, (size_t)width * 4,
                               (size_t)height, hipMemcpyHostToDevice, s)) != hipSuccess)
       return c->hip_fail(e, "fingerprint upload");
-    Kd = reinterpret_cast<const float*>(kdev.ptr);
+    Kd = reinterpret_cast<const float*>(c->stage_tight.ptr);
     rs = width;
   }
-  void* FK = nullptr;
-  if ((e = work.reserve((size_t)padded_frame(height, width) * sizeof(float))) != hipSuccess ||
-      (e = inter.reserve((size_t)height * tiled_cols(sh) * sizeof(c32))) != hipSuccess ||
-      (e = sums.reserve((size_t)(height + 2) * sizeof(double))) != hipSuccess ||
-      (e = stats.reserve(2 * sizeof(double))) != hipSuccess ||
-      (e = small.reserve(sizeof(CandParam) + sizeof(FrameRef))) != hipSuccess ||
-      (e = hipMalloc(&FK, (size_t)height * tiled_cols(sh) * sizeof(c32))) != hipSuccess)
-    return fail(PRNU_E_NOMEM, "fingerprint buffers: %s", hipGetErrorString(e));
-  struct {
+  struct Small {
+    double stats[2];  // mean, norm
     CandParam id;
     FrameRef wref;
-  } hsmall = {CandParam{1.f, 0.f, 0, 0}, FrameRef{work.ptr, nullptr}};
+  };
+  const size_t fk_bytes = (size_t)height * tiled_cols(sh) * sizeof(c32);
+  const size_t sums_bytes = 2 * (size_t)(height + 2) * sizeof(double);
+  if ((e = c->stage_dev.reserve((size_t)padded_frame(height, width) * sizeof(float))) != hipSuccess ||
+      (e = c->fp_small.reserve(sizeof(Small) + sums_bytes)) != hipSuccess)
+    return fail(PRNU_E_NOMEM, "fingerprint buffers: %s", hipGetErrorString(e));
+  if ((st = c->runner.ensure_workspace(sh, 1)) != PRNU_OK) return st;
+  void* FK = c->alloc_spectrum(fk_bytes, &e);
+  if (!FK) return fail(PRNU_E_NOMEM, "fingerprint buffers: %s", hipGetErrorString(e));
+  const Small hs = {{0.0, 0.0}, CandParam{1.f, 0.f, 0, 0}, FrameRef{c->stage_dev.ptr, nullptr}};
   double hstats[2] = {0, 0};
-  const CandParam* did = reinterpret_cast<const CandParam*>(small.ptr);
-  const FrameRef* dref = reinterpret_cast<const FrameRef*>(reinterpret_cast<char*>(small.ptr) + sizeof(CandParam));
-  if ((e = hipMemcpyAsync(small.ptr, &hsmall, sizeof(hsmall), hipMemcpyHostToDevice, s)) != hipSuccess ||
-      (e = launch_fp_prepare(Kd, rs, sh, reinterpret_cast<float*>(work.ptr), reinterpret_cast<c32*>(inter.ptr),
-                             reinterpret_cast<double*>(sums.ptr), reinterpret_cast<double*>(stats.ptr),
-                             reinterpret_cast<c32*>(FK), twM, twMi, twN, did, dref, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(hstats, stats.ptr, sizeof(hstats), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+  Small* ds = reinterpret_cast<Small*>(c->fp_small.ptr);
+  double* sums = reinterpret_cast<double*>(ds + 1);
+  if ((e = c->upload(ds, &hs, sizeof(hs))) != hipSuccess ||
+      (e = launch_fp_prepare(Kd, rs, sh, reinterpret_cast<float*>(c->stage_dev.ptr),
+                             reinterpret_cast<c32*>(c->runner.ws_inter.ptr), sums, ds->stats,
+                             reinterpret_cast<c32*>(FK), twM, twMi, twN, &ds->id, &ds->wref, s)) != hipSuccess ||
+      (e = hipMemcpyAsync(hstats, ds->stats, sizeof(hstats), hipMemcpyDeviceToHost, s)) != hipSuccess ||
       (e = hipStreamSynchronize(s)) != hipSuccess) {
     (void)hipFree(FK);
     return c->hip_fail(e, "fingerprint preparation");
   }
   if (!std::isfinite(hstats[0]) || !std::isfinite(hstats[1])) {
-    (void)hipFree(FK);
+    std::lock_guard<std::mutex> lf(c->fp_mu);
+    c->free_spectrum(FK, fk_bytes);
     return fail(PRNU_E_NONFINITE, "fingerprint holds NaN or Inf");
   }
   Fingerprint f;
@@ -1400,8 +1450,11 @@ prnu_status prnu_close_fingerprint(prnu_ctx* ctx, prnu_fp fp) {
   if (it == c->fps.end()) return fail(PRNU_E_HANDLE, "unknown fingerprint %llu", (unsigned long long)fp);
   if (it->second.users > 0) return fail(PRNU_E_BUSY, "fingerprint has videos in flight");
   (void)hipSetDevice(c->device);
-  (void)hipStreamSynchronize(c->runner.stream);
-  (void)hipFree(it->second.FK);
+  // whatever still reads the spectrum (the allocation-free scoring runs on the caller's
+  // streams) has finished before it is used again
+  (void)hipDeviceSynchronize();
+  const Shape sh{it->second.M, it->second.N, 0};
+  c->free_spectrum(it->second.FK, (size_t)sh.M * tiled_cols(sh) * sizeof(c32));
   c->fps.erase(it);
   return PRNU_OK;
 }

@@ -213,7 +213,8 @@ class Context {
   prnu_fp next_fp = 0;
 
   Runner runner;  // synchronous path
-  DevBuf stage_dev, stage_tight, stage_scale, dev_cand, dev_rec, dev_frefs, dev_fprefs, dev_proj;
+  DevBuf stage_dev, stage_tight, stage_scale, dev_cand, dev_rec, dev_frefs, dev_proj;
+  FpRef* dev_fprefs = nullptr;      // behind the frame table in dev_frefs
   // synchronous searches: items, candidate lists, fallback list, chain state, results
   DevBuf dev_items, dev_outs, dev_site, dev_fbc, dev_fbs, dev_fbr, dev_ndev, dev_state, dev_best, dev_res, dev_lists;
   HostBuf host_items, host_outs, host_res, host_lists;
@@ -221,6 +222,16 @@ class Context {
   HostBuf stage_pinned;             // pinned staging of host frames for the synchronous calls
   HostBuf res_pinned, res_pinned_out;  // residual extraction: pinned input and output staging
   HostBuf host_cand, host_rec, host_refs;
+  DevBuf fp_small;                  // fingerprint preparation: row sums, statistics, tables
+  // Spectra of closed fingerprints, kept for the next one of the same size: at most
+  // kMaxSpectra bytes in all (under fp_mu).
+  std::vector<std::pair<void*, size_t>> fk_spare;
+  static constexpr size_t kMaxSpectra = (size_t)64 << 20;
+  void* alloc_spectrum(size_t bytes, hipError_t* err);
+  void free_spectrum(void* p, size_t bytes);  // nothing queued may still use it
+  // Events that order a library stream after a caller's, reused between calls.
+  std::mutex ev_mu;
+  std::vector<hipEvent_t> ev_spare;
 
   std::unique_ptr<ServingEngine, ServingDeleter> serving;
 
@@ -240,6 +251,10 @@ class Context {
   prnu_status refine(const Shape& sh, int dtype, int F, const prnu_search_opts* o,
                      const std::vector<std::pair<double, double>>& inits, prnu_frame_result* out);
   prnu_status upload_refs(const std::vector<FrameRef>& frames, const Fingerprint& fp);
+  // n bytes of host memory to the device on the synchronous stream.  Small tables travel
+  // as a kernel's argument (no DMA, and the host memory is free at once); larger ones are
+  // copied, and `host` (pinned) must stay until the stream has run.
+  hipError_t upload(void* dst, const void* host, size_t n);
   ServingEngine* engine();
   void shutdown_serving();
   // Schedule of a shape, tuned on runner r at first use unless tuning is off.
