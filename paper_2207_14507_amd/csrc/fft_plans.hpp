@@ -3,10 +3,17 @@
 // Row plans run on pairs of real rows packed into one complex row (length N = frame
 // width), one transform per workgroup of 64 threads (128 for widths 1280 and 1920, 256
 // for 3840); the first radix is chosen so that the first pass maps one butterfly onto
-// each thread.  Column plans run on strips of 8 interleaved columns of the packed half
+// each thread.  Widths of 256 and less take three small radices instead of two large
+// ones, because a first radix of 8 to 16 leaves a wave 8 to 16 butterflies, each with all
+// its samples to gather: 256 = 4 x 8 x 8 (64 butterflies) runs the row kernel in 0.117
+// instead of 0.186 us per candidate of 256 x 256 (16 x 16), the band kernel in 0.064
+// instead of 0.082.  Column plans run on strips of 8 interleaved columns of the packed half
 // spectrum (length M = frame height) with 256 threads (512 for 720 and 1080; from 1280
 // rows on, each 4-column half of a strip on 256 or 512 threads); their radices keep most
-// lanes busy with few butterflies per thread.  At 1080 and 2160 rows the plans were
+// lanes busy with few butterflies per thread (heights of 256 and less: three small
+// radices keep all four waves busy, 256 = 8 x 4 x 8 0.123 us per candidate against 0.135
+// as 16 x 16, 160 = 5 x 8 x 4 0.067 against 0.079, 120 = 5 x 6 x 4 0.056 against 0.071 on
+// 256-wide frames).  At 1080 and 2160 rows the plans were
 // picked by timing the alternatives on the device: an odd last radix (the inverse
 // transform's first, whose stores a radix apart then fall on distinct LDS banks; at 1080
 // rows an odd first radix too) with a large middle radix beats the plans that keep every
@@ -46,11 +53,11 @@ struct ColPlan;
     static_assert(RS::count >= 2, "at least two passes");    \
   };
 
-PRNU_PLAN(RowPlan, 64, 8, 8)
-PRNU_PLAN(RowPlan, 96, 12, 8)
-PRNU_PLAN(RowPlan, 120, 15, 8)
-PRNU_PLAN(RowPlan, 160, 10, 16)
-PRNU_PLAN(RowPlan, 256, 16, 16)
+PRNU_PLAN(RowPlan, 64, 2, 4, 8)
+PRNU_PLAN(RowPlan, 96, 3, 4, 8)
+PRNU_PLAN(RowPlan, 120, 3, 5, 8)
+PRNU_PLAN(RowPlan, 160, 4, 5, 8)
+PRNU_PLAN(RowPlan, 256, 4, 8, 8)
 PRNU_PLAN(RowPlan, 720, 12, 6, 10)
 PRNU_PLAN(RowPlan, 1080, 15, 8, 9)
 PRNU_PLAN(RowPlan, 1280, 10, 16, 8)
@@ -58,11 +65,11 @@ PRNU_PLAN(RowPlan, 1920, 15, 8, 16)
 PRNU_PLAN(RowPlan, 2160, 15, 12, 12)
 PRNU_PLAN(RowPlan, 3840, 15, 16, 16)
 
-PRNU_PLAN(ColPlan, 64, 8, 8)
-PRNU_PLAN(ColPlan, 96, 8, 12)
-PRNU_PLAN(ColPlan, 120, 8, 15)
-PRNU_PLAN(ColPlan, 160, 10, 16)
-PRNU_PLAN(ColPlan, 256, 16, 16)
+PRNU_PLAN(ColPlan, 64, 4, 4, 4)
+PRNU_PLAN(ColPlan, 96, 4, 6, 4)
+PRNU_PLAN(ColPlan, 120, 5, 6, 4)
+PRNU_PLAN(ColPlan, 160, 5, 8, 4)
+PRNU_PLAN(ColPlan, 256, 8, 4, 8)
 PRNU_PLAN_PFA(ColPlan, 720, 16, 9, 5)
 PRNU_PLAN_PFA(ColPlan, 1080, 27, 8, 5)
 PRNU_PLAN(ColPlan, 1280, 16, 8, 10)
