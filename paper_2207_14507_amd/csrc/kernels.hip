@@ -1143,7 +1143,7 @@ constexpr int row_threads() {
 }
 template <int M>
 constexpr int col_threads() {
-  return M >= 1920 || M == 1080 || M == 720 ? 512 : 256;
+  return M >= 720 ? 512 : 256;
 }
 
 // Workgroups of a device-counted launch of a chunk of `tiles` tiles: one per tile

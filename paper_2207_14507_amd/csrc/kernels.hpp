@@ -84,8 +84,11 @@ __host__ __device__ constexpr inline int col_split(int M) { return M >= 1280 ? 2
 // Column workgroups (and energy partial sums) per candidate.
 __host__ __device__ inline int col_blocks(const Shape& s) { return col_strips(s) * col_split(s.M); }
 
-// Wavefronts of a row transform's workgroup.
-__host__ __device__ constexpr inline int row_waves(int N) { return N >= 3840 ? 4 : (N >= 1280 ? 2 : 1); }
+// Wavefronts of a row transform's workgroup: as many as one round of its first pass's
+// butterflies fills (fft_plans.hpp).
+__host__ __device__ constexpr inline int row_waves(int N) {
+  return N >= 3840 ? 4 : (N >= 2160 ? 3 : (N >= 1280 ? 2 : 1));
+}
 // Largest window values per candidate: one per band row pair and wavefront of its
 // workgroup.
 __host__ __device__ inline int peak_parts(const Shape& s) { return s.band_pairs() * row_waves(s.N); }

@@ -228,6 +228,31 @@ def test_small_shapes_ragged_strips_and_batches(P, M, N, R):
         P.prnu_destroy(c)
 
 
+@pytest.mark.parametrize("shape,frame_shape,R", [((64, 2160), (64, 2160), 20), ((96, 2160), (90, 2011), 8),
+                                                 ((64, 2160), (64, 2160), 0)])
+def test_rows_of_three_waves(P, ctx, shape, frame_shape, R):
+    """Width 2160: row transforms and window rows on three waves (equal and padded frames,
+    host-counted and device-counted launches)."""
+    seq = synth.cropped_sequence(23, shape, frame_shape, 2, radius=max(1, R - 2))
+    grid = (5, 0.97, 1.03, 5, -1.0, 1.0)
+    opts = P.make_opts(grid=grid, radius=R)
+    fp = P.prnu_open_fingerprint(ctx, seq.K)
+    say(f"shape {shape} frames {frame_shape} R={R}")
+    pce, rho, dx, dy = P.prnu_score_grid(ctx, fp, seq.frames, 0, opts)
+    cands = O.candidates(O.grid_values(*grid[:3]), O.grid_values(*grid[3:]))
+    o_pce, o_dx, o_dy, o_gap, rs, near = oracle_scores(seq.K, seq.frames[0], cands, R)
+    check_candidates(f"{shape}", pce, dx, dy, o_pce, o_dx, o_dy, o_gap, near)
+    assert np.allclose(rho, [r.rho for r in rs], rtol=1e-3, atol=1e-6)
+    res, _ = P.prnu_search_frames(ctx, fp, seq.frames, opts)
+    check_argmax(f"{shape}", o_pce, res[0].cand_index)
+    # the second frame of the chain takes the fallback, whose candidates are counted on the device
+    warm = P.make_opts(grid=grid, radius=R, warm=True, local=(3, 3, 0.005, 0.1), fallback_pce=1e12)
+    chain, _ = P.prnu_search_frames(ctx, fp, seq.frames, warm)
+    assert (chain[0].cand_index, chain[0].pce) == (res[0].cand_index, res[0].pce)
+    assert chain[1].fell_back == 1 and chain[1].pce >= res[1].pce
+    P.prnu_close_fingerprint(ctx, fp)
+
+
 def test_bf16_residuals_match_oracle_on_dequantised_values(P, ctx):
     seq = synth.tiny(n_frames=2, config=22)
     q = [synth.quantize_bf16(f) for f in seq.frames]
