@@ -60,3 +60,29 @@ def test_noise_free_model_and_device_inputs(P):
         assert e.value.status == P.PRNU_E_SHAPE
     finally:
         P.prnu_destroy(ctx)
+
+
+@pytest.mark.parametrize("L,M,N", [(1, 1, 1), (2, 1, 3), (5, 1, 5), (3, 5, 7), (4, 3, 341), (6, 33, 31), (9, 41, 25)])
+def test_estimate_of_images_aligned_to_a_float(P, L, M, N):
+    """Pixel counts that are no multiple of 4 (the images after the first lie 4-byte
+    aligned), from one pixel to a few past a workgroup's 1024, images and residuals on one
+    stream and from device and host memory: the double sums' result rounded to float32."""
+    import torch
+    g = np.random.default_rng(7 * L + M)
+    I = g.uniform(0.0, 255.0, (L, M, N)).astype(np.float32)
+    W = g.normal(0.0, 2.0, (L, M, N)).astype(np.float32)
+    ctx = P.prnu_create(0)
+    try:
+        ref = O.estimate_fingerprint(I, W)
+        assert np.allclose(P.prnu_estimate_fingerprint(ctx, I, W), ref, rtol=2e-7, atol=1e-9)
+        out = torch.full((M, N), 7.0, device="cuda")
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            di, dw = torch.from_numpy(I).cuda(), torch.from_numpy(W).cuda()
+            P.prnu_estimate_fingerprint(ctx, di, dw, out=out)
+        assert np.allclose(out.cpu().numpy(), ref, rtol=2e-7, atol=1e-9)
+        out.fill_(7.0)
+        P.prnu_estimate_fingerprint(ctx, di, W, out=out)
+        assert np.allclose(out.cpu().numpy(), ref, rtol=2e-7, atol=1e-9)
+    finally:
+        P.prnu_destroy(ctx)
