@@ -86,3 +86,22 @@ def test_estimate_of_images_aligned_to_a_float(P, L, M, N):
         assert np.allclose(out.cpu().numpy(), ref, rtol=2e-7, atol=1e-9)
     finally:
         P.prnu_destroy(ctx)
+
+
+@pytest.mark.parametrize("L,M,N", [(13, 1579, 1558), (13, 1580, 1560), (13, 1571, 1571)])
+def test_estimate_past_the_last_level_cache(P, L, M, N):
+    """Just under (255.8 MB) and past (256.3 and 256.7 MB) 256 MB of images and residuals,
+    the loads' aligned and unaligned forms."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    I = torch.rand((L, M, N), generator=g, device="cuda")
+    W = torch.randn((L, M, N), generator=g, device="cuda")
+    out = torch.empty((M, N), device="cuda")
+    ctx = P.prnu_create(0)
+    try:
+        P.prnu_estimate_fingerprint(ctx, I, W, out=out)
+        rows = np.r_[0:3, M // 2, M - 3:M]
+        ref = O.estimate_fingerprint(I[:, rows].cpu().numpy(), W[:, rows].cpu().numpy())
+        assert np.allclose(out[rows].cpu().numpy(), ref, rtol=2e-7, atol=1e-9)
+    finally:
+        P.prnu_destroy(ctx)
