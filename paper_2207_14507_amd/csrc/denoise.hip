@@ -18,6 +18,8 @@
 //
 // All arithmetic is fp32.  Every kernel is a streaming pass: its input tile and halo
 // are read once, its outputs written once.
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace prnu {
@@ -44,9 +46,11 @@ __device__ __forceinline__ int wrap(int i, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// Forward level.  Output tile: FY rows x FX columns of each subband.
+// Forward level.  Output tile: FY rows x FX columns of each subband.  512 threads: the
+// deep levels' few tiles are bound by the length of a thread's work, one call of 3 images
+// of 333 x 501 6 us shorter than on 256, and the large levels are no slower.
 
-constexpr int FY = 16, FX = 32, FT = 256;
+constexpr int FY = 16, FX = 32, FT = 512;
 constexpr int FIY = 2 * FY + 6, FIX = 2 * FX + 6;  // input tile with the filter's reach
 
 // in: level input plane of rows x cols (row stride in_rs, image stride in_is); at level 1
@@ -132,19 +136,17 @@ __global__ __launch_bounds__(FT) void k_dwt_fwd(const float* __restrict__ in, in
 // by its vector instructions (issue slots 76% busy: 18 per raw coefficient, 38 per
 // result), where the variances as a pass of their own took 88 us and wrote and read
 // 200 MB more, and the inverse after it 88 us.  64 x 96: a raw column per lane with both
-// halos (59 of 64 lanes, 51 of them results); 32 rows cost 6% more at 1080p (more halo)
-// for 4% less at 333 x 501.  With the raw tile in LDS and nine reads per coefficient and
+// halos (59 of 64 lanes, 51 of them results); 32 rows where a level has few tiles
+// (launch_residuals).  With the raw tile in LDS and nine reads per coefficient and
 // row the kernel took 115 us, two columns per thread 140 us (106 VGPRs, two workgroups
 // per CU instead of three).
-constexpr int IY = 64, IX = 96;
-constexpr int CY = IY / 2 + 3, CX = IX / 2 + 3;
-constexpr int WH = 4;            // the 9 x 9 window's reach
-constexpr int WN = IY / 16;      // runs of rows per subband
-constexpr int WR = (CY + WN - 1) / WN;           // rows of a run
-constexpr int WRE = (IY / 2 + WN - 2) / (WN - 1);  // rows of a run in a tile of the first rows
+constexpr int IX = 96;
+constexpr int CX = IX / 2 + 3;
+constexpr int WH = 4;       // the 9 x 9 window's reach
+constexpr int WN = 4;       // runs of rows per subband
 constexpr int IT = 3 * WN * 64;
-static_assert(CX + 2 * WH <= 64 && 7 + WH + IX / 2 + WH <= 64, "a raw column per lane, wrapped ones too");
 constexpr int VS = CX | 1;  // LDS row stride of the vertical synthesis (read at every second column)
+static_assert(CX + 2 * WH <= 64 && 7 + WH + IX / 2 + WH <= 64, "a raw column per lane, wrapped ones too");
 
 // v of the previous (next) lane, zero into the first (last).
 __device__ __forceinline__ float lane_prev(float v) {
@@ -168,6 +170,9 @@ __device__ __forceinline__ float removed(float c, float t3, float t5, float t7, 
 template <int R>
 __device__ __forceinline__ void wiener_rows(const float* src, int64_t rs, unsigned x, bool xin, int n, int ro, int rows,
                                             float s2, float* out, bool put) {
+  // the squares rounded before they are summed, whatever R: a coefficient's part is the
+  // same bits in every tile and run it may fall in
+#pragma clang fp contract(off)
   const int first = n < 0 ? -ro : 0;  // the subband's first row in the run's numbering
   float v[R + 8], h[4][R + 8];
 #pragma unroll
@@ -232,10 +237,14 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 // residual keeps none of the coarsest); det: coefficient planes, quadrants as in
 // k_dwt_fwd.  out: rows x cols plane (stride out_rs, image stride out_is), only its first
 // M rows and N columns written.
+template <int IY>
 __global__ __launch_bounds__(IT, 6) void k_dwt_inv(const float* __restrict__ ll, int64_t ll_is, int64_t ll_rs,
                                                      const float* __restrict__ det, int64_t det_is, int64_t det_rs,
                                                      int rows, int cols, int M, int N, float s2,
                                                      float* __restrict__ out, int64_t out_is, int64_t out_rs) {
+  constexpr int CY = IY / 2 + 3;
+  constexpr int WR = (CY + WN - 1) / WN;             // rows of a run
+  constexpr int WRE = (IY / 2 + WN - 2) / (WN - 1);  // rows of a run in a tile of the first rows
   __shared__ float s[3][CY][CX], a[CY][CX];  // removed parts (LH, HL, HH) and LL
   __shared__ float vl[IY][VS], vh[IY][VS];   // vertical synthesis
   const int img = blockIdx.z, tid = threadIdx.x;
@@ -396,8 +405,19 @@ hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L
       dst = l % 2 == 0 ? T1 : T2;
       dis = per, drs = cols, mm = rows, nn = cols;
     }
-    dim3 grid((unsigned)((cols + IX - 1) / IX), (unsigned)((rows + IY - 1) / IY), (unsigned)L);
-    k_dwt_inv<<<grid, IT, 0, s>>>(src_ll, per, cols / 2, C, per, N2, rows, cols, mm, nn, s2, dst, dis, drs);
+    // A level of at most one tile of 64 rows per CU takes tiles of 32, whose work is half
+    // as long on twice the CUs: a call of 3 images of 333 x 501 84 -> 76 us, of one of
+    // 64 x 64 (its deep levels hold subbands shorter than 7) 123 -> 93.  Everywhere they
+    // would cost 16 images of 1080 x 1920 270 -> 302 us (more halo).
+    auto inv = [&](auto iy) {
+      constexpr int IY = decltype(iy)::value;
+      dim3 grid((unsigned)((cols + IX - 1) / IX), (unsigned)((rows + IY - 1) / IY), (unsigned)L);
+      k_dwt_inv<IY><<<grid, IT, 0, s>>>(src_ll, per, cols / 2, C, per, N2, rows, cols, mm, nn, s2, dst, dis, drs);
+    };
+    if ((int64_t)((cols + IX - 1) / IX) * ((rows + 63) / 64) * L <= 256)
+      inv(std::integral_constant<int, 32>());
+    else
+      inv(std::integral_constant<int, 64>());
   }
   return hipGetLastError();
 }

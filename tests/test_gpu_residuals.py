@@ -81,6 +81,19 @@ def test_residuals_at_the_inverse_tiles_edges(P, ctx, M, N):
         check(f"{M}x{N} image {l}", W[l], I[l], 3.0)
 
 
+@pytest.mark.parametrize("M,N,L", [(64, 96, 256), (64, 96, 257), (65, 97, 300), (130, 290, 300), (112, 112, 300),
+                                   (16, 640, 300), (40, 50, 300)])
+def test_residuals_of_many_and_of_few_tiles_agree(P, ctx, M, N, L):
+    """Levels of up to 256 tiles and of more take tiles of different heights; the sums are
+    the same, and so are the bits.  Images alone (few tiles) are checked against the oracle."""
+    I, _ = images(9, 3, M, N)
+    many = P.prnu_extract_residuals(ctx, np.concatenate([np.resize(I, (L - 3, M, N)), I]), 3.0)
+    for l in range(3):
+        W = P.prnu_extract_residuals(ctx, I[l:l + 1], 3.0)[0]
+        check(f"{M}x{N} image {l}", W, I[l], 3.0)
+        assert np.array_equal(many[l], W) and np.array_equal(many[L - 3 + l], W)
+
+
 @pytest.mark.parametrize("sigma0", [0.5, 10.0, 1e4])
 def test_other_noise_levels(P, ctx, sigma0):
     I, _ = images(2, 1, 96, 160)
