@@ -3,6 +3,7 @@
 // warm-start chain around them (chain.hip), and the synchronous searches.  The serving
 // engine (submit / poll) lives in serving.hip.
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -47,6 +48,7 @@ hipError_t DevBuf::reserve(size_t n) {
   release();
   hipError_t e = hipMalloc(&ptr, n);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // the caller has the error: the next launch must not find it
     ptr = nullptr;
     return e;
   }
@@ -65,6 +67,7 @@ hipError_t HostBuf::reserve(size_t n) {
   release();
   hipError_t e = hipHostMalloc(&ptr, n, hipHostMallocDefault);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     ptr = nullptr;
     return e;
   }
@@ -254,33 +257,63 @@ int Runner::batch_size(const Shape& sh) const {
   return std::max(1, std::min(256, b));
 }
 
+// Bytes of the workspace buffers ws_inter .. ws_peak for nc candidates.
+static std::array<size_t, Runner::kWorkspace> workspace_parts(const Shape& sh, int nc) {
+  const size_t n = (size_t)nc;
+  return {n * sh.M * tiled_cols(sh) * sizeof(c32),          n * sh.band_rows() * sh.Nh() * sizeof(c32),
+          n * sh.band_rows() * sh.win_cols() * sizeof(float), n * sh.row_pairs() * sizeof(double2),
+          n * col_blocks(sh) * sizeof(double),              n * peak_parts(sh) * sizeof(float)};
+}
+
 size_t Runner::workspace_bytes(const Shape& sh, int nc) const {
-  return (size_t)nc * ((size_t)sh.M * tiled_cols(sh) * sizeof(c32) + (size_t)sh.band_rows() * sh.Nh() * sizeof(c32) +
-                       (size_t)sh.band_rows() * sh.win_cols() * sizeof(float) +
-                       (size_t)sh.row_pairs() * sizeof(double2) + (size_t)col_blocks(sh) * sizeof(double) +
-                       (size_t)peak_parts(sh) * sizeof(float));
+  size_t sum = 0;
+  for (size_t b : workspace_parts(sh, nc)) sum += b;
+  return sum;
 }
 
 prnu_status Runner::ensure_workspace(const Shape& sh, int nc) {
+  const auto need = workspace_parts(sh, nc);
+  DevBuf* const ws[] = {&ws_inter, &ws_band, &ws_win, &ws_norm, &ws_energy, &ws_peak};
   hipError_t e;
-  const bool grow = (size_t)nc * sh.M * tiled_cols(sh) * sizeof(c32) > ws_inter.cap ||
-                    (size_t)nc * sh.band_rows() * sh.Nh() * sizeof(c32) > ws_band.cap ||
-                    (size_t)nc * sh.band_rows() * sh.win_cols() * sizeof(float) > ws_win.cap ||
-                    (size_t)nc * sh.row_pairs() * sizeof(double2) > ws_norm.cap ||
-                    (size_t)nc * col_blocks(sh) * sizeof(double) > ws_energy.cap ||
-                    (size_t)nc * peak_parts(sh) * sizeof(float) > ws_peak.cap;
+  bool grow = false;
+  for (int i = 0; i < kWorkspace; ++i) grow |= need[i] > ws[i]->cap;
   // Launches already queued on this stream may still use the buffers about to be
   // replaced: let them finish first.
   if (grow && (e = hipStreamSynchronize(stream)) != hipSuccess)
     return fail(PRNU_E_DEVICE, "workspace: %s", hipGetErrorString(e));
-  if ((e = ws_inter.reserve((size_t)nc * sh.M * tiled_cols(sh) * sizeof(c32))) != hipSuccess ||
-      (e = ws_band.reserve((size_t)nc * sh.band_rows() * sh.Nh() * sizeof(c32))) != hipSuccess ||
-      (e = ws_win.reserve((size_t)nc * sh.band_rows() * sh.win_cols() * sizeof(float))) != hipSuccess ||
-      (e = ws_norm.reserve((size_t)nc * sh.row_pairs() * sizeof(double2))) != hipSuccess ||
-      (e = ws_energy.reserve((size_t)nc * col_blocks(sh) * sizeof(double))) != hipSuccess ||
-      (e = ws_peak.reserve((size_t)nc * peak_parts(sh) * sizeof(float))) != hipSuccess)
-    return fail(PRNU_E_NOMEM, "workspace: %s", hipGetErrorString(e));
+  for (int i = 0; i < kWorkspace; ++i)
+    if ((e = ws[i]->reserve(need[i])) != hipSuccess) return fail(PRNU_E_NOMEM, "workspace: %s", hipGetErrorString(e));
   return PRNU_OK;
+}
+
+// The workspace for nc candidates where the card has memory to spare, else (false) the
+// present one, untouched.  A refused size is not asked for again.
+bool Runner::grow_workspace(Context& ctx, const Shape& sh, int nc) {
+  auto need = workspace_parts(sh, nc);
+  DevBuf* const ws[] = {&ws_inter, &ws_band, &ws_win, &ws_norm, &ws_energy, &ws_peak};
+  size_t bytes = 0;
+  for (int i = 0; i < kWorkspace; ++i)
+    if (need[i] > ws[i]->cap) bytes += need[i];
+  if (bytes == 0) return true;
+  const size_t total = workspace_bytes(sh, nc);
+  if (total >= grow_refused) return false;
+  // a sixteenth of the card stays free for allocations that cannot do with less
+  size_t free_b = 0, card_b = 0;
+  bool ok = hipMemGetInfo(&free_b, &card_b) == hipSuccess && free_b >= bytes + card_b / 16;
+  if (ctx.inject(ctx.fault_grow, ctx.n_grow)) need[0] = kImpossible;
+  DevBuf fresh[kWorkspace];
+  for (int i = 0; ok && i < kWorkspace; ++i)
+    if (need[i] > ws[i]->cap) ok = fresh[i].reserve(need[i]) == hipSuccess;
+  // launches already queued on this stream may still use the buffers to be replaced
+  ok = ok && hipStreamSynchronize(stream) == hipSuccess;
+  if (!ok) {
+    (void)hipGetLastError();
+    grow_refused = total;
+    return false;
+  }
+  for (int i = 0; i < kWorkspace; ++i)
+    if (fresh[i].ptr) ws[i]->swap(fresh[i]);
+  return true;
 }
 
 static Batch make_batch(const Runner& r, const Shape& sh, int dtype, const FrameRef* frames, const FpRef* fps,
@@ -435,7 +468,7 @@ prnu_status Runner::run_dyn(Context& ctx, const Shape& sh, int dtype, const Fram
     // Every chunk is four launches whether it holds work or not (about 25 us when it does
     // not): a list somewhat longer than a batch is one chunk where the workspace limit
     // and the memory left allow (the full grid's 861 candidates against batches of 768).
-    if (ensure_workspace(sh, n_max) == PRNU_OK) sc.chunk = n_max;
+    if (grow_workspace(ctx, sh, n_max)) sc.chunk = n_max;
   }
   if ((st = ensure_workspace(sh, std::min(sc.chunk, n_max))) != PRNU_OK) return st;
   const c32* twM = ctx.twiddles(kColPlan, sh.M);
@@ -1331,7 +1364,7 @@ prnu_status prnu_create(const prnu_config* cfg, prnu_ctx** out) {
   if (c->max_slots <= 0) c->max_slots = 16;
   if (const char* b = std::getenv("PRNU_BATCH")) c->runner.batch_override = std::atoi(b);
   if (const char* f = std::getenv("PRNU_FAULT")) {
-    // comma-separated "launch:N" and "stage:N"
+    // comma-separated "launch:N", "stage:N" and "grow:N"
     std::string spec(f);
     for (size_t pos = 0; pos < spec.size();) {
       size_t end = spec.find(',', pos);
@@ -1342,6 +1375,7 @@ prnu_status prnu_create(const prnu_config* cfg, prnu_ctx** out) {
         const long long n = std::atoll(item.c_str() + colon + 1);
         if (item.compare(0, colon, "launch") == 0) c->fault_launch = n;
         if (item.compare(0, colon, "stage") == 0) c->fault_stage = n;
+        if (item.compare(0, colon, "grow") == 0) c->fault_grow = n;
       }
       pos = end + 1;
     }

@@ -25,6 +25,10 @@ struct DevBuf {
   size_t cap = 0;
   hipError_t reserve(size_t n);
   void release();
+  void swap(DevBuf& o) {
+    std::swap(ptr, o.ptr);
+    std::swap(cap, o.cap);
+  }
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -141,6 +145,9 @@ constexpr int kMergeGen = 2048;
 struct Runner {
   hipStream_t stream = nullptr;
   DevBuf ws_inter, ws_band, ws_win, ws_norm, ws_energy, ws_peak;
+  static constexpr int kWorkspace = 6;      // those buffers
+  size_t grow_refused = ~(size_t)0;         // smallest workspace grow_workspace was refused
+  static constexpr size_t kImpossible = (size_t)1 << 60;
   double batch_bytes = 512.0 * 1024 * 1024;
   int batch_override = 0;
   bool prof_on = false;
@@ -164,6 +171,7 @@ struct Runner {
   void drop_graphs();
   size_t workspace_bytes(const Shape& sh, int nc) const;
   prnu_status ensure_workspace(const Shape& sh, int nc);
+  bool grow_workspace(Context& ctx, const Shape& sh, int nc);
   // Candidates [0, n) of cand (device) with records to rec (device); proj (device, 9
   // floats per candidate, or null) selects the general Eq. (4) form.
   prnu_status run(Context& ctx, const Shape& sh, int dtype, const FrameRef* frames, const FpRef* fps,
@@ -194,11 +202,12 @@ class Context {
   std::mutex fp_mu;  // fingerprint table
   std::mutex tw_mu;  // twiddle tables
   std::atomic<bool> failed{false};
-  // Host-side fault hook for tests (PRNU_FAULT=launch:N,stage:N): the Nth launch of
+  // Host-side fault hook for tests (PRNU_FAULT=launch:N,stage:N,grow:N): the Nth launch of
   // search kernels, or the Nth frame staging, on this context fails as a device error
-  // does, before any of its work is issued.  0 = off.
-  int64_t fault_launch = 0, fault_stage = 0;
-  std::atomic<int64_t> n_launch{0}, n_stage{0};
+  // does, before any of its work is issued; the Nth optional growth of a workspace asks
+  // for more memory than there is.  0 = off.
+  int64_t fault_launch = 0, fault_stage = 0, fault_grow = 0;
+  std::atomic<int64_t> n_launch{0}, n_stage{0}, n_grow{0};
   bool inject(int64_t at, std::atomic<int64_t>& count) { return at > 0 && ++count == at; }
   uint64_t hbm_budget = 0;
   int max_slots = 0;

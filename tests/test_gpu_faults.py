@@ -99,3 +99,36 @@ def test_staging_fault(P):
         expect_device_error(P, P.prnu_score_grid, ctx, fp, seq.frames, 0, opts)
     finally:
         P.prnu_destroy(ctx)
+
+
+@pytest.mark.parametrize("spec", ["grow:1", "grow:2"])
+def test_a_refused_larger_workspace_leaves_the_smaller_batches(P, spec):
+    """A fallback grid of 361 candidates against batches of 256 asks for one larger
+    workspace; where the card has no room for it, the chain runs in the batches it had,
+    with the same results, in that call and in later ones.  (The second growth, of another
+    shape, on a workspace that already grew once.)"""
+    opts = P.make_opts(grid=(19, 0.97, 1.03, 19, -1.0, 1.0), radius=16, warm=True, local=(3, 3, 0.005, 0.2),
+                       fallback_pce=1e12)
+    seqs = [synth.walk_sequence(73, i, M, N, 3, radius=8) for i, (M, N) in enumerate([(160, 160), (256, 256)])]
+
+    def run(ctx):
+        out = []
+        for s in seqs + seqs[:1]:
+            fp = P.prnu_open_fingerprint(ctx, s.K)
+            out += [(r.status, r.cand_index, r.fell_back, r.n_evaluated, r.pce, r.rho, r.dx, r.dy)
+                    for r in P.prnu_search_frames(ctx, fp, s.frames, opts)[0]]
+            P.prnu_close_fingerprint(ctx, fp)
+        return out
+
+    ctx = P.prnu_create(0, flags=P.PRNU_FLAG_NO_AUTOTUNE)
+    try:
+        want = run(ctx)
+    finally:
+        P.prnu_destroy(ctx)
+    assert all(w[0] == 0 for w in want) and sum(w[2] for w in want) == 6
+    ctx = faulty_context(P, spec)
+    try:
+        assert run(ctx) == want
+        assert run(ctx) == want
+    finally:
+        P.prnu_destroy(ctx)
