@@ -192,6 +192,9 @@ int32_t prnu_supported_lengths(int32_t* out, int32_t cap);
  * it needs; *out receives a handle. */
 prnu_status prnu_open_fingerprint(prnu_ctx* ctx, const float* K, int32_t height, int32_t width,
                                   int64_t row_stride, int32_t on_device, void* stream, prnu_fp* out);
+/* Waits for the device (scoring that still reads the fingerprint runs to its end) and
+ * closes the handle.  PRNU_E_DEVICE, the handle closed all the same, if that wait meets a
+ * device error that no earlier call has reported. */
 prnu_status prnu_close_fingerprint(prnu_ctx* ctx, prnu_fp fp);
 
 /* The grid search of Sec. 3.2 on every frame of one video against fingerprint fp

@@ -1364,7 +1364,7 @@ prnu_status prnu_create(const prnu_config* cfg, prnu_ctx** out) {
   if (c->max_slots <= 0) c->max_slots = 16;
   if (const char* b = std::getenv("PRNU_BATCH")) c->runner.batch_override = std::atoi(b);
   if (const char* f = std::getenv("PRNU_FAULT")) {
-    // comma-separated "launch:N", "stage:N" and "grow:N"
+    // comma-separated "launch:N", "stage:N", "grow:N" and "close:N"
     std::string spec(f);
     for (size_t pos = 0; pos < spec.size();) {
       size_t end = spec.find(',', pos);
@@ -1376,6 +1376,7 @@ prnu_status prnu_create(const prnu_config* cfg, prnu_ctx** out) {
         if (item.compare(0, colon, "launch") == 0) c->fault_launch = n;
         if (item.compare(0, colon, "stage") == 0) c->fault_stage = n;
         if (item.compare(0, colon, "grow") == 0) c->fault_grow = n;
+        if (item.compare(0, colon, "close") == 0) c->fault_close = n;
       }
       pos = end + 1;
     }
@@ -1486,10 +1487,20 @@ prnu_status prnu_close_fingerprint(prnu_ctx* ctx, prnu_fp fp) {
   (void)hipSetDevice(c->device);
   // whatever still reads the spectrum (the allocation-free scoring runs on the caller's
   // streams) has finished before it is used again
-  (void)hipDeviceSynchronize();
+  const hipError_t e = c->inject(c->fault_close, c->n_close) ? hipErrorUnknown : hipDeviceSynchronize();
   const Shape sh{it->second.M, it->second.N, 0};
-  c->free_spectrum(it->second.FK, (size_t)sh.M * tiled_cols(sh) * sizeof(c32));
+  if (e == hipSuccess) {
+    c->free_spectrum(it->second.FK, (size_t)sh.M * tiled_cols(sh) * sizeof(c32));
+  } else {
+    // not known to be idle: no later fingerprint may be written over it
+    (void)hipFree(it->second.FK);
+    (void)hipGetLastError();
+  }
   c->fps.erase(it);
+  // A wait refused while a caller's stream is captured is no failure of the device; one
+  // that an earlier call has reported is not reported again, so that a failed context can
+  // be cleaned up.
+  if (e != hipSuccess && e != hipErrorStreamCaptureUnsupported && !c->failed) return c->hip_fail(e, "fingerprint close");
   return PRNU_OK;
 }
 

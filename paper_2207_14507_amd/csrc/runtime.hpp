@@ -202,12 +202,13 @@ class Context {
   std::mutex fp_mu;  // fingerprint table
   std::mutex tw_mu;  // twiddle tables
   std::atomic<bool> failed{false};
-  // Host-side fault hook for tests (PRNU_FAULT=launch:N,stage:N,grow:N): the Nth launch of
-  // search kernels, or the Nth frame staging, on this context fails as a device error
-  // does, before any of its work is issued; the Nth optional growth of a workspace asks
-  // for more memory than there is.  0 = off.
-  int64_t fault_launch = 0, fault_stage = 0, fault_grow = 0;
-  std::atomic<int64_t> n_launch{0}, n_stage{0}, n_grow{0};
+  // Host-side fault hook for tests (PRNU_FAULT=launch:N,stage:N,grow:N,close:N): the Nth
+  // launch of search kernels, or the Nth frame staging, on this context fails as a device
+  // error does, before any of its work is issued; the Nth optional growth of a workspace
+  // asks for more memory than there is; the Nth closing of a fingerprint does not wait and
+  // takes its wait for failed.  0 = off.
+  int64_t fault_launch = 0, fault_stage = 0, fault_grow = 0, fault_close = 0;
+  std::atomic<int64_t> n_launch{0}, n_stage{0}, n_grow{0}, n_close{0};
   bool inject(int64_t at, std::atomic<int64_t>& count) { return at > 0 && ++count == at; }
   uint64_t hbm_budget = 0;
   int max_slots = 0;

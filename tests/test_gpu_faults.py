@@ -132,3 +132,20 @@ def test_a_refused_larger_workspace_leaves_the_smaller_batches(P, spec):
         assert run(ctx) == want
     finally:
         P.prnu_destroy(ctx)
+
+
+def test_a_failed_wait_on_closing_poisons_the_context(P):
+    """A spectrum whose readers are not known to have finished is not handed on, and the
+    device error is not lost."""
+    seq = synth.tiny(n_frames=1, config=74)
+    ctx = faulty_context(P, "close:2")
+    try:
+        first, second = P.prnu_open_fingerprint(ctx, seq.K), P.prnu_open_fingerprint(ctx, seq.K)
+        P.prnu_close_fingerprint(ctx, first)
+        expect_device_error(P, P.prnu_close_fingerprint, ctx, second)
+        expect_device_error(P, P.prnu_open_fingerprint, ctx, seq.K)
+        with pytest.raises(P.PrnuError) as e:
+            P.prnu_close_fingerprint(ctx, second)
+        assert e.value.status == P.PRNU_E_HANDLE   # closed all the same
+    finally:
+        P.prnu_destroy(ctx)

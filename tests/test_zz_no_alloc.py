@@ -106,3 +106,43 @@ def test_noalloc_bf16_frames_smaller_than_the_fingerprint(P):
         P.prnu_close_fingerprint(ctx, fp)
     finally:
         P.prnu_destroy(ctx)
+
+
+def test_closing_waits_for_scoring_queued_on_the_callers_stream(P):
+    """A fingerprint closed, and another opened in its place, while an allocation-free
+    scoring of the first is still queued behind other work on the caller's stream: the
+    scores are those of the first."""
+    import torch
+    seqs = [synth.walk_sequence(5, i, 256, 256, 1, radius=8) for i in range(2)]
+    opts = P.make_opts(grid=(5, 0.97, 1.03, 5, -1.0, 1.0), radius=16)
+    n = 25
+    ctx = P.prnu_create(0)
+    try:
+        want = []
+        for s in seqs:
+            fp = P.prnu_open_fingerprint(ctx, s.K)
+            want.append(P.prnu_score_grid(ctx, fp, seqs[0].frames, 0, opts))
+            P.prnu_close_fingerprint(ctx, fp)
+        assert not np.array_equal(want[0][0], want[1][0])
+        frames = torch.from_numpy(seqs[0].frames).cuda()
+        x = torch.randn((4096, 4096), device="cuda")
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for rep in range(3):
+            say("rep", rep)
+            fp = P.prnu_open_fingerprint(ctx, seqs[0].K)
+            out = [torch.zeros(n, dtype=t, device="cuda") for t in (torch.float64, torch.float64, torch.int32, torch.int32)]
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                for _ in range(20):
+                    y = x @ x
+                P.prnu_score_grid_noalloc(ctx, fp, frames, 0, opts, *out)
+            P.prnu_close_fingerprint(ctx, fp)
+            fp = P.prnu_open_fingerprint(ctx, seqs[1].K)
+            got = P.prnu_score_grid(ctx, fp, seqs[0].frames, 0, opts)
+            torch.cuda.synchronize()
+            same("queued", [t.cpu().numpy() for t in out], want[0])
+            same("in its place", got, want[1])
+            P.prnu_close_fingerprint(ctx, fp)
+    finally:
+        P.prnu_destroy(ctx)
