@@ -43,15 +43,52 @@ double now_s() {
 // ---------------------------------------------------------------------------
 // Buffers.
 
+// Spectra of closed fingerprints, which nothing queued reads any more, kept for the next
+// fingerprint of the same size: at most kMaxSpectra bytes per context.  In one list for
+// all contexts, so that any device allocation that finds no room can give them back.
+namespace {
+constexpr size_t kMaxSpectra = (size_t)64 << 20;
+struct Spare {
+  const Context* owner;
+  int device;
+  void* ptr;
+  size_t bytes;
+};
+std::mutex g_spare_mu;  // taken last
+std::vector<Spare> g_spares;
+
+// Frees the spares that gone() picks; whether there were any.
+template <class F>
+bool drop_spares(F gone) {
+  std::lock_guard<std::mutex> lk(g_spare_mu);
+  const auto at = std::stable_partition(g_spares.begin(), g_spares.end(), [&](const Spare& x) { return !gone(x); });
+  const bool any = at != g_spares.end();
+  for (auto i = at; i != g_spares.end(); ++i) (void)hipFree(i->ptr);
+  g_spares.erase(at, g_spares.end());
+  return any;
+}
+
+// hipMalloc on the current device; without room, again after its spare spectra are given
+// back.  The error is returned, not left behind for the next launch to find.
+hipError_t device_alloc(void** p, size_t n) {
+  hipError_t e = hipMalloc(p, n);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  int dev = -1;
+  if (hipGetDevice(&dev) == hipSuccess && drop_spares([&](const Spare& x) { return x.device == dev; }) &&
+      (e = hipMalloc(p, n)) == hipSuccess)
+    return e;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return e;
+}
+}  // namespace
+
 hipError_t DevBuf::reserve(size_t n) {
   if (n <= cap) return hipSuccess;
   release();
-  hipError_t e = hipMalloc(&ptr, n);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();  // the caller has the error: the next launch must not find it
-    ptr = nullptr;
-    return e;
-  }
+  hipError_t e = device_alloc(&ptr, n);
+  if (e != hipSuccess) return e;
   cap = n;
   return hipSuccess;
 }
@@ -740,7 +777,7 @@ const c32* Context::twiddles(int kind, int L) {
   std::vector<c32> h((size_t)n);
   twiddle_table(kind, L, h.data(), n);
   void* d = nullptr;
-  if (hipMalloc(&d, (size_t)n * sizeof(c32)) != hipSuccess) return nullptr;
+  if (device_alloc(&d, (size_t)n * sizeof(c32)) != hipSuccess) return nullptr;
   if (hipMemcpy(d, h.data(), (size_t)n * sizeof(c32), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(d);
     return nullptr;
@@ -797,31 +834,32 @@ hipError_t Context::upload(void* dst, const void* host, size_t n) {
 }
 
 void* Context::alloc_spectrum(size_t bytes, hipError_t* err) {
-  std::lock_guard<std::mutex> lk(fp_mu);
-  for (size_t i = 0; i < fk_spare.size(); ++i)
-    if (fk_spare[i].second == bytes) {
-      void* p = fk_spare[i].first;
-      fk_spare.erase(fk_spare.begin() + (long)i);
-      *err = hipSuccess;
-      return p;
-    }
+  {
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    for (auto i = g_spares.begin(); i != g_spares.end(); ++i)
+      if (i->owner == this && i->bytes == bytes) {
+        void* p = i->ptr;
+        g_spares.erase(i);
+        *err = hipSuccess;
+        return p;
+      }
+  }
   void* p = nullptr;
-  if ((*err = hipMalloc(&p, bytes)) == hipSuccess) return p;
-  if (fk_spare.empty()) return nullptr;
-  // give the spare spectra back and try again
-  for (auto& x : fk_spare) (void)hipFree(x.first);
-  fk_spare.clear();
-  (void)hipGetLastError();
-  return (*err = hipMalloc(&p, bytes)) == hipSuccess ? p : nullptr;
+  *err = device_alloc(&p, bytes);
+  return p;
 }
 
 void Context::free_spectrum(void* p, size_t bytes) {
-  size_t held = 0;
-  for (auto& x : fk_spare) held += x.second;
-  if (held + bytes <= kMaxSpectra)
-    fk_spare.emplace_back(p, bytes);
-  else
-    (void)hipFree(p);
+  {
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    size_t held = 0;
+    for (const Spare& x : g_spares) held += x.owner == this ? x.bytes : 0;
+    if (held + bytes <= kMaxSpectra) {
+      g_spares.push_back(Spare{this, device, p, bytes});
+      return;
+    }
+  }
+  (void)hipFree(p);
 }
 
 // F host frames of M x N elements of esz bytes (frame and row strides in elements) into
@@ -1307,7 +1345,7 @@ Context::~Context() {
   shutdown_serving();
   for (auto& kv : tw) (void)hipFree(kv.second);
   for (auto& kv : fps) (void)hipFree(kv.second.FK);
-  for (auto& x : fk_spare) (void)hipFree(x.first);
+  (void)drop_spares([this](const Spare& x) { return x.owner == this; });
   for (hipEvent_t ev : ev_spare) (void)hipEventDestroy(ev);
   if (runner.stream) (void)hipStreamDestroy(runner.stream);
 }
@@ -1459,7 +1497,6 @@ prnu_status prnu_open_fingerprint(prnu_ctx* ctx, const float* K, int32_t height,
     return c->hip_fail(e, "fingerprint preparation");
   }
   if (!std::isfinite(hstats[0]) || !std::isfinite(hstats[1])) {
-    std::lock_guard<std::mutex> lf(c->fp_mu);
     c->free_spectrum(FK, fk_bytes);
     return fail(PRNU_E_NONFINITE, "fingerprint holds NaN or Inf");
   }

@@ -233,12 +233,10 @@ class Context {
   HostBuf res_pinned, res_pinned_out;  // residual extraction: pinned input and output staging
   HostBuf host_cand, host_rec, host_refs;
   DevBuf fp_small;                  // fingerprint preparation: row sums, statistics, tables
-  // Spectra of closed fingerprints, kept for the next one of the same size: at most
-  // kMaxSpectra bytes in all (under fp_mu).
-  std::vector<std::pair<void*, size_t>> fk_spare;
-  static constexpr size_t kMaxSpectra = (size_t)64 << 20;
+  // A fingerprint's spectrum, from the spare ones if there is one of the size; given back
+  // to them (nothing queued may still use it).
   void* alloc_spectrum(size_t bytes, hipError_t* err);
-  void free_spectrum(void* p, size_t bytes);  // nothing queued may still use it
+  void free_spectrum(void* p, size_t bytes);
   // Events that order a library stream after a caller's, reused between calls.
   std::mutex ev_mu;
   std::vector<hipEvent_t> ev_spare;

@@ -149,3 +149,32 @@ def test_a_failed_wait_on_closing_poisons_the_context(P):
         assert e.value.status == P.PRNU_E_HANDLE   # closed all the same
     finally:
         P.prnu_destroy(ctx)
+
+
+def test_spare_spectra_are_given_back_when_memory_is_short(P):
+    """The spectra kept from closed fingerprints, of any context on the device, make room
+    for whatever cannot be allocated."""
+    import torch
+    seq = synth.walk_sequence(75, 0, 160, 160, 2, radius=8)
+    wide = synth.fingerprint(synth.rng(75), 1080, 1920)
+    small, large = (P.make_opts(grid=(n, 0.97, 1.03, n, -1.0, 1.0), radius=16, warm=True, local=(3, 3, 0.005, 0.2),
+                                fallback_pce=1e12) for n in (16, 19))
+    other = P.prnu_create(0, flags=P.PRNU_FLAG_NO_AUTOTUNE)
+    ctx = faulty_context(P, "grow:1")
+    try:
+        for c in (other, ctx):   # 8.3 MB each
+            P.prnu_close_fingerprint(c, P.prnu_open_fingerprint(c, wide))
+        fp = P.prnu_open_fingerprint(ctx, seq.K)
+        P.prnu_search_frames(ctx, fp, seq.frames, small)   # batches of 256, as large as the next search's
+        before = torch.cuda.mem_get_info()[0]
+        res, _ = P.prnu_search_frames(ctx, fp, seq.frames, large)   # asks for one of 361, refused
+        assert [r.status for r in res] == [0, 0] and res[1].fell_back == 1
+        freed = torch.cuda.mem_get_info()[0] - before
+        say("freed", freed)
+        assert freed > 12 << 20
+        # both contexts go on: spectra are allocated anew
+        for c in (other, ctx):
+            P.prnu_close_fingerprint(c, P.prnu_open_fingerprint(c, wide))
+    finally:
+        P.prnu_destroy(ctx)
+        P.prnu_destroy(other)
