@@ -1305,8 +1305,11 @@ prnu_status Context::score_full(const Shape& sh, int dtype, const prnu_grid& g, 
 // array in the code object, so that the call itself allocates nothing.  In host code
 // `scratch` only names the symbol; its device address, one per device, comes from
 // hipGetSymbolAddress at context creation and is what the kernels receive.
+// What fits is decided on kScratchBytes; the peak values of the band rows, under 0.5% of a
+// candidate's workspace, lie behind them.
 constexpr size_t kScratchBytes = (size_t)128 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kPeakBytes = (size_t)1 << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kPeakBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -1630,19 +1633,19 @@ prnu_status prnu_score_grid_noalloc(prnu_ctx* ctx, prnu_fp fp, const prnu_frames
                b_win = (size_t)sh.band_rows() * sh.win_cols() * sizeof(float),
                b_norm = (size_t)sh.row_pairs() * sizeof(double2), b_energy = (size_t)col_blocks(sh) * sizeof(double),
                b_peak = (size_t)peak_parts(sh) * sizeof(float);
-  const size_t per = b_inter + b_band + b_win + b_norm + b_energy + b_peak;
-  const size_t slack = 6 * 256;
+  const size_t per = b_inter + b_band + b_win + b_norm + b_energy;
+  const size_t slack = 5 * 256;
   if (o_ws + slack + per > kScratchBytes)
     return fail(PRNU_E_NOMEM, "frame %dx%d against %dx%d needs more than the %zu-byte scratch", frames->height,
                 frames->width, sh.M, sh.N, kScratchBytes);
-  const int chunk = (int)std::min<size_t>((size_t)n, (kScratchBytes - o_ws - slack) / per);
+  const int chunk = (int)std::min({(size_t)n, (kScratchBytes - o_ws - slack) / per, kPeakBytes / b_peak});
   unsigned char* ws = base + o_ws;
   c32* inter = reinterpret_cast<c32*>(ws);
   c32* band = reinterpret_cast<c32*>(ws + round256(b_inter * chunk));
   float* win = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(band) + round256(b_band * chunk));
   double2* norm = reinterpret_cast<double2*>(reinterpret_cast<unsigned char*>(win) + round256(b_win * chunk));
   double* energy = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(norm) + round256(b_norm * chunk));
-  float* peak = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(energy) + round256(b_energy * chunk));
+  float* peak = reinterpret_cast<float*>(base + kScratchBytes);
   hipStream_t s = reinterpret_cast<hipStream_t>(frames->stream);
   // frame table, fingerprint table and the grid's item, written by a kernel from its
   // arguments

@@ -146,3 +146,26 @@ def test_closing_waits_for_scoring_queued_on_the_callers_stream(P):
             P.prnu_close_fingerprint(ctx, fp)
     finally:
         P.prnu_destroy(ctx)
+
+
+@pytest.mark.parametrize("frame_shape,R,fits", [((2160, 3834), 790, True), ((2160, 3840), 788, True),
+                                                ((2160, 3840), 789, False)])
+def test_noalloc_at_the_scratch_arrays_limit(P, frame_shape, R, fits):
+    """4K fp32 frames whose workspace fills the scratch array to its last kilobytes, and
+    one that it does not hold."""
+    g = synth.rng(77)
+    K = synth.fingerprint(g, 2160, 3840)
+    frames = g.standard_normal((1, *frame_shape), dtype=np.float32)
+    opts = P.make_opts(grid=(3, 0.99, 1.01, 3, -0.5, 0.5), radius=R)
+    ctx = P.prnu_create(0, flags=P.PRNU_FLAG_NO_AUTOTUNE)
+    try:
+        fp = P.prnu_open_fingerprint(ctx, K)
+        if not fits:
+            with pytest.raises(P.PrnuError) as e:
+                noalloc_scores(P, ctx, fp, frames, 0, opts)
+            assert e.value.status == P.PRNU_E_NOMEM
+            return
+        ref = P.prnu_score_grid(ctx, fp, frames, 0, opts)
+        same(f"{frame_shape} R {R}", noalloc_scores(P, ctx, fp, frames, 0, opts), ref)
+    finally:
+        P.prnu_destroy(ctx)
