@@ -146,6 +146,7 @@ constexpr int WH = 4;       // the 9 x 9 window's reach
 constexpr int WN = 4;       // runs of rows per subband
 constexpr int IT = 3 * WN * 64;
 constexpr int VS = CX | 1;  // LDS row stride of the vertical synthesis (read at every second column)
+static_assert(9 * CX <= IT && 9 * (64 / 2 + 3) <= IT, "wrapped places of short subbands: one per thread");
 static_assert(CX + 2 * WH <= 64 && 7 + WH + IX / 2 + WH <= 64, "a raw column per lane, wrapped ones too");
 
 // v of the previous (next) lane, zero into the first (last).
@@ -208,29 +209,6 @@ __device__ __forceinline__ void wiener_rows(const float* src, int64_t rs, unsign
   }
 }
 
-// The removed part of the coefficient (n, m) of a subband of ro x co, element by element:
-// for subbands shorter than 7, which a tile of the first rows or columns holds several
-// times over.
-__device__ __forceinline__ float wiener_small(const float* src, int64_t rs, int n, int m, int ro, int co, float s2) {
-  float t3 = 0.f, t5 = 0.f, t7 = 0.f, t9 = 0.f;
-#pragma unroll 1
-  for (int a = -WH; a <= WH; ++a) {
-    if (n + a < 0 || n + a >= ro) continue;
-#pragma unroll 1
-    for (int b = -WH; b <= WH; ++b) {
-      if (m + b < 0 || m + b >= co) continue;
-      const float v = src[(int64_t)(n + a) * rs + m + b];
-      const int w = max(abs(a), abs(b));
-      const float q = v * v;
-      t9 += q;
-      t7 += w <= 3 ? q : 0.f;
-      t5 += w <= 2 ? q : 0.f;
-      t3 += w <= 1 ? q : 0.f;
-    }
-  }
-  return removed(src[(int64_t)n * rs + m], t3, t5, t7, t9, s2);
-}
-
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // ll: approximation plane (ro x co, stride ll_rs, image stride ll_is) or null (zero: the
@@ -251,6 +229,11 @@ __global__ __launch_bounds__(IT, 6) void k_dwt_inv(const float* __restrict__ ll,
   const int ro = rows / 2, co = cols / 2;
   const int y0 = blockIdx.y * IY, x0 = blockIdx.x * IX;
   const int n0 = y0 / 2 - 3, m0 = x0 / 2 - 3;
+  // A subband shorter than 7 (then the level is one tile in that direction): the far end's
+  // last seven would hold a column twice, so each is computed once and the wrapped places
+  // are copied afterwards (a call of one 96 x 96 image 74 us, of 640 x 16 74, of 112 x 112
+  // 74; with every place of the tile summed element by element 116 and 166).
+  const bool few_rows = ro < 3 + WH, few_cols = co < 3 + WH;
   {
     // the wave's index, and with it every row's address, in scalar registers
     const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -265,32 +248,31 @@ __global__ __launch_bounds__(IT, 6) void k_dwt_inv(const float* __restrict__ ll,
     const int band = w / WN, run = w % WN;
     const float* src = d + (band == 1 ? 0 : (int64_t)ro * det_rs) + (band == 0 ? 0 : co);
     float* sb = &s[band][0][0];
-    if (min(ro, co) < 3 + WH) {
-      for (int i = run * 64 + lane; i < CY * CX; i += WN * 64)
-        sb[i] = wiener_small(src, det_rs, wrap(n0 + i / CX, ro), wrap(m0 + i % CX, co), ro, co, s2);
+    // The lane's column.  In a tile of the first columns, lanes 0..6 hold the far end's
+    // last seven (the synthesis is periodic, the windows are not), four lanes zeros; of a
+    // subband of fewer columns each is held once.
+    int m = m0 - WH + lane;
+    bool in = m < co && lane < CX + 2 * WH, res = lane >= WH && lane < WH + CX;
+    if (few_cols) {
+      m = lane - WH;
+      in = res = m >= 0 && m < co;
+    } else if (m0 < 0) {
+      const bool far = lane < 7;
+      m = far ? lane - 7 : lane - 7 - WH;
+      in = far || (m >= 0 && m < co && m < IX / 2 + WH);
+      res = far ? m >= -3 : m >= 0 && m < IX / 2;
+    }
+    const unsigned x = in ? (unsigned)(m < 0 ? m + co : m) : 0u;
+    float* o = sb + (res ? m - m0 : 0);
+    if (n0 < 0) {
+      // a tile of the first rows: the far end's last three are a run of their own
+      if (run > 0)
+        wiener_rows<WRE>(src, det_rs, x, in, (run - 1) * WRE, ro, min(WRE, IY / 2 - (run - 1) * WRE), s2,
+                         o + (3 + (run - 1) * WRE) * CX, res);
+      else if (!few_rows)
+        wiener_rows<3>(src, det_rs, x, in, -3, ro, 3, s2, o, res);
     } else {
-      // The lane's column.  In a tile of the first columns, lanes 0..6 hold the far end's
-      // last seven (the synthesis is periodic, the windows are not), four lanes zeros.
-      int m = m0 - WH + lane;
-      bool in = m < co && lane < CX + 2 * WH, res = lane >= WH && lane < WH + CX;
-      if (m0 < 0) {
-        const bool far = lane < 7;
-        m = far ? lane - 7 : lane - 7 - WH;
-        in = far || (m >= 0 && m < co && m < IX / 2 + WH);
-        res = far ? m >= -3 : m >= 0 && m < IX / 2;
-      }
-      const unsigned x = in ? (unsigned)(m < 0 ? m + co : m) : 0u;
-      float* o = sb + (res ? m - m0 : 0);
-      if (n0 < 0) {
-        // a tile of the first rows: the far end's last three are a run of their own
-        if (run == 0)
-          wiener_rows<3>(src, det_rs, x, in, -3, ro, 3, s2, o, res);
-        else
-          wiener_rows<WRE>(src, det_rs, x, in, (run - 1) * WRE, ro, min(WRE, IY / 2 - (run - 1) * WRE), s2,
-                           o + (3 + (run - 1) * WRE) * CX, res);
-      } else {
-        wiener_rows<WR>(src, det_rs, x, in, n0 + run * WR, ro, min(WR, CY - run * WR), s2, o + run * WR * CX, res);
-      }
+      wiener_rows<WR>(src, det_rs, x, in, n0 + run * WR, ro, min(WR, CY - run * WR), s2, o + run * WR * CX, res);
     }
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
@@ -299,6 +281,19 @@ __global__ __launch_bounds__(IT, 6) void k_dwt_inv(const float* __restrict__ ll,
     }
   }
   __syncthreads();
+  if (few_rows || few_cols) {
+    // the places before the first row or column, from the subband's last three (or fewer)
+    auto col = [&](int c) { return few_cols && c < 3 ? 3 + wrap(c - 3, co) : c; };
+    if (few_rows && tid < 9 * CX) {
+      const int b = tid / (3 * CX), r = tid / CX % 3, c = tid % CX;
+      s[b][r][c] = s[b][3 + wrap(r - 3, ro)][col(c)];
+    }
+    if (few_cols && tid < 9 * CY) {
+      const int b = tid / (3 * CY), r = tid / 3 % CY, c = tid % 3;
+      if (!few_rows || r >= 3) s[b][r][c] = s[b][r][col(c)];
+    }
+    __syncthreads();
+  }
   // vertical: output row y takes coefficient rows y/2 - j (j = 0..3) with taps y%2 + 2j
   // (y0 is even).  A thread takes one coefficient column and 8 output rows, which
   // need 7 coefficient rows of each subband: read into registers once.
@@ -406,9 +401,8 @@ hipError_t launch_residuals(const float* in, int64_t in_is, int64_t in_rs, int L
       dis = per, drs = cols, mm = rows, nn = cols;
     }
     // A level of at most one tile of 64 rows per CU takes tiles of 32, whose work is half
-    // as long on twice the CUs: a call of 3 images of 333 x 501 84 -> 76 us, of one of
-    // 64 x 64 (its deep levels hold subbands shorter than 7) 123 -> 93.  Everywhere they
-    // would cost 16 images of 1080 x 1920 270 -> 302 us (more halo).
+    // as long on twice the CUs: a call of 3 images of 333 x 501 84 -> 76 us.  Everywhere
+    // they would cost 16 images of 1080 x 1920 270 -> 302 us (more halo).
     auto inv = [&](auto iy) {
       constexpr int IY = decltype(iy)::value;
       dim3 grid((unsigned)((cols + IX - 1) / IX), (unsigned)((rows + IY - 1) / IY), (unsigned)L);

@@ -153,3 +153,39 @@ def test_residual_errors(P, ctx):
             P.prnu_extract_residuals(ctx, I, s)
         assert e.value.status == P.PRNU_E_ARG
     assert P.prnu_extract_residuals(ctx, I[:0], 3.0).shape == (0, 32, 32)
+
+
+@pytest.mark.parametrize("M,N", [(12, 25), (32, 47), (20, 300), (300, 20), (80, 1600), (1600, 80), (95, 200), (33, 96)])
+@pytest.mark.parametrize("L", [2, 260])
+def test_subbands_shorter_than_the_windows_reach(P, ctx, M, N, L):
+    """One to six coefficient rows or columns or both, of several levels, beside one and
+    several tiles in the other direction, in tiles of either height."""
+    I, _ = images(10, 2, M, N)
+    W = P.prnu_extract_residuals(ctx, np.concatenate([I[:1], np.resize(I, (L - 1, M, N))]), 3.0)
+    check(f"{M}x{N} image 0", W[0], I[0], 3.0)
+    check(f"{M}x{N} image {L - 1}", W[L - 1], I[(L - 2) % 2], 3.0)
+
+
+@pytest.mark.parametrize("short,full", [((96, 96), (112, 112)), ((16, 640), (112, 640)), ((640, 16), (640, 112)),
+                                        ((80, 1600), (112, 1600))])
+def test_images_of_a_short_side_cost_no_more(P, ctx, short, full):
+    """The same launches on fewer pixels.  A quarter more is allowed for the timer; computing
+    the short subbands' windows element by element took half as much again and more."""
+    import time
+
+    import torch
+    data = []
+    for M, N in (short, full):
+        I = torch.from_numpy(images(11, 1, M, N)[0]).cuda()
+        data.append((I, torch.empty_like(I)))
+    best = [math.inf, math.inf]
+    for _ in range(12):
+        for k, (I, out) in enumerate(data):
+            for _ in range(5):
+                P.prnu_extract_residuals(ctx, I, 3.0, out=out)
+            t = time.perf_counter()
+            for _ in range(20):
+                P.prnu_extract_residuals(ctx, I, 3.0, out=out)
+            best[k] = min(best[k], time.perf_counter() - t)
+    say(f"{short}: {best[0] / 20 * 1e6:.1f} us, {full}: {best[1] / 20 * 1e6:.1f} us")
+    assert best[0] <= 1.25 * best[1]
