@@ -253,6 +253,30 @@ def test_rows_of_three_waves(P, ctx, shape, frame_shape, R):
     P.prnu_close_fingerprint(ctx, fp)
 
 
+@pytest.mark.parametrize("shape,frame_shape,R", [((64, 2160), (64, 2160), 20), ((96, 2160), (90, 2011), 8),
+                                                 ((64, 2160), (64, 2160), 0), ((720, 1280), (720, 1280), 16),
+                                                 ((64, 3840), (60, 3700), 12)])
+def test_device_counted_scores_are_the_host_counted_ones(P, ctx, shape, frame_shape, R):
+    """Chains whose local grid is one node at the full grid's corner, which every frame
+    falls back from: what the fallback's device-counted launches score decides, and has
+    to be what the plain search of the frame finds."""
+    seq = synth.cropped_sequence(24, shape, frame_shape, 3, radius=max(1, R - 2))
+    grid = (5, 0.97, 1.03, 5, -1.0, 1.0)
+    fp = P.prnu_open_fingerprint(ctx, seq.K)
+    pce, _, _, _ = P.prnu_score_grid(ctx, fp, seq.frames, 0, P.make_opts(grid=grid, radius=R))
+    want, _ = P.prnu_search_frames(ctx, fp, seq.frames, P.make_opts(grid=grid, radius=R))
+    corner = (0.97, -1.0)
+    assert want[0].cand_index == int(np.argmax(pce)) != 0 and pce[0] < want[0].pce
+    warm = P.make_opts(grid=grid, radius=R, warm=True, local=(1, 1, 0.005, 0.1), fallback_pce=1e12, init=corner)
+    chain, _ = P.prnu_search_frames(ctx, fp, seq.frames, warm)
+    for f, (r, w) in enumerate(zip(chain, want)):
+        say(f"{shape} f{f}: ({r.scale}, {r.rot_deg}) ({r.dx}, {r.dy}) PCE {r.pce:.3f}")
+        assert r.fell_back == 1 and r.n_evaluated == 26
+        assert (r.pce, r.rho, r.dx, r.dy) == (w.pce, w.rho, w.dx, w.dy)
+        assert math.isclose(r.scale, w.scale, abs_tol=1e-12) and math.isclose(r.rot_deg, w.rot_deg, abs_tol=1e-12)
+    P.prnu_close_fingerprint(ctx, fp)
+
+
 def test_bf16_residuals_match_oracle_on_dequantised_values(P, ctx):
     seq = synth.tiny(n_frames=2, config=22)
     q = [synth.quantize_bf16(f) for f in seq.frames]

@@ -135,3 +135,26 @@ def test_every_schedule_gives_the_same_results(P, tmp_path):
                 assert [fields(r) for r in res] == [fields(r) for r in ref], (batch, order)
             finally:
                 P.prnu_destroy(ctx)
+
+
+@pytest.mark.parametrize("ns,nr", [(64, 32), (41, 50), (67, 31)])
+@pytest.mark.parametrize("fallback", [0.0, 1e12])
+def test_large_local_grids_in_a_chain(P, ns, nr, fallback):
+    """Local grids of 2048 candidates, which one block generates behind the previous frame,
+    and of 2050 and 2077, which take a launch of their own: the chain is the frames searched
+    one by one, each started from the last one's result."""
+    s = synth.walk_sequence(43, 0, 64, 64, 4, radius=4)
+    kw = dict(grid=(5, 0.97, 1.03, 5, -1.0, 1.0), radius=8, warm=True, local=(ns, nr, 0.001, 0.05), fallback_pce=fallback)
+    ctx = P.prnu_create(0, flags=P.PRNU_FLAG_NO_AUTOTUNE)
+    try:
+        fp = P.prnu_open_fingerprint(ctx, s.K)
+        chain, _ = P.prnu_search_frames(ctx, fp, s.frames, P.make_opts(**kw))
+        init = None
+        for f in range(4):
+            one, _ = P.prnu_search_frames(ctx, fp, s.frames[f:f + 1], P.make_opts(init=init, **kw))
+            assert fields(chain[f]) == fields(one[0]), f
+            assert one[0].n_evaluated == (25 if f == 0 else ns * nr + (25 if one[0].fell_back else 0))
+            init = (one[0].scale, one[0].rot_deg)
+        say(ns, nr, [r.fell_back for r in chain])
+    finally:
+        P.prnu_destroy(ctx)
