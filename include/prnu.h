@@ -46,10 +46,13 @@
  *     call on it returns PRNU_E_DEVICE.
  *   - Threading: all calls on one context are thread-safe.
  *   - Test hook: the environment variable PRNU_FAULT, read by prnu_create, takes a
- *     comma-separated list of "launch:N" and "stage:N".  The Nth launch of search
- *     kernels (or the Nth frame staging) on that context then fails the way a HIP
- *     failure does (PRNU_E_DEVICE, the context marked failed, every video in the
- *     serving engine ended with PRNU_E_DEVICE) before any of its work is issued.
+ *     comma-separated list of "launch:N", "stage:N", "close:N" and "grow:N".  The Nth
+ *     launch of search kernels (or the Nth frame staging) on that context then fails the
+ *     way a HIP failure does (PRNU_E_DEVICE, the context marked failed, every video in
+ *     the serving engine ended with PRNU_E_DEVICE) before any of its work is issued; the
+ *     Nth closing of a fingerprint fails that way after it has closed the handle; the
+ *     Nth time the library would take a larger workspace than it needs, it is refused
+ *     the memory (and goes on in the one it has).
  */
 #ifndef PRNU_H_
 #define PRNU_H_
@@ -219,11 +222,12 @@ prnu_status prnu_score_grid(prnu_ctx* ctx, prnu_fp fp, const prnu_frames* frames
  * n_scale * n_rot entries.  The work is queued on frames->stream (NULL: the legacy
  * default stream) and the call returns without waiting: the outputs are valid once that
  * stream has run it.  Intermediate data live in a fixed 128 MiB device array of the
- * library (one per device, held until the process ends), shared by every call on that
- * device: calls that overlap on one device (from any thread or context, on any streams)
- * race and must not be issued.  Limits: at most 65536 candidates, and the zero-bordered
+ * library (one per device, with 1 MiB behind it, held until the process ends), shared by
+ * every call on that device: calls that overlap on one device (from any thread or
+ * context, on any streams) race and must not be issued.  Limits: at most 65536 candidates, and the zero-bordered
  * frame, the candidate lists and one candidate's workspace must fit the array (every
- * shape the library supports does).  The fingerprint's transform tables exist once
+ * shape the library supports does, at 2160 x 3840 in float32 up to a shift radius of
+ * 788).  The fingerprint's transform tables exist once
  * prnu_open_fingerprint has returned.  Errors: as prnu_score_grid, plus PRNU_E_ARG for
  * host frames or too many candidates and PRNU_E_NOMEM when the scratch array is too
  * small; nothing is queued then. */

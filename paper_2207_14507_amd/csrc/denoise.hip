@@ -16,8 +16,10 @@
 //               coarsest level: the residual keeps none of it) the adjoint transform
 //               (periodic); level 1 writes the cropped residual.
 //
-// All arithmetic is fp32.  Every kernel is a streaming pass: its input tile and halo
-// are read once, its outputs written once.
+// All arithmetic is fp32.  Every kernel is a streaming pass whose outputs are written once.
+// The forward reads its input tile and halo once; a wave of the inverse reads the 8 halo
+// rows of its run of coefficient rows itself (17 rows for 9 results in tiles of 64 rows, 13
+// for 5 in tiles of 32; the neighbouring run's waves leave them in cache).
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -137,9 +139,9 @@ __global__ __launch_bounds__(FT) void k_dwt_fwd(const float* __restrict__ in, in
 // result), where the variances as a pass of their own took 88 us and wrote and read
 // 200 MB more, and the inverse after it 88 us.  64 x 96: a raw column per lane with both
 // halos (59 of 64 lanes, 51 of them results); 32 rows where a level has few tiles
-// (launch_residuals).  With the raw tile in LDS and nine reads per coefficient and
-// row the kernel took 115 us, two columns per thread 140 us (106 VGPRs, two workgroups
-// per CU instead of three).
+// (launch_residuals).  A CU holds two workgroups of 12 waves (68 VGPRs, 55 kB of LDS
+// each at 64 rows).  With the raw tile in LDS and nine reads per coefficient and row the
+// kernel took 115 us, two columns per thread 140 us (106 VGPRs).
 constexpr int IX = 96;
 constexpr int CX = IX / 2 + 3;
 constexpr int WH = 4;       // the 9 x 9 window's reach
